@@ -145,6 +145,9 @@ typedef struct bf_plan_s *bf_plan;   /* opaque, owned by libbf */
  * with real data; a wavefront then covers tile[0] x tile[1] x 2 tile[2]
  * points, the default for such plans; a grid whose depth axis is not along
  * the array normal runs BF_DAS_LDS instead, as bf_plan_get_info reports).
+ * HERCULES plans whose aperture and grid are symmetric about the array centre
+ * give each lane the mirror images of its point instead (two or four points
+ * of one depth; BF_DAS_LDS_Z2 then covers tile[2] depths per wavefront too).
  * Results agree to FP32 rounding; the variants differ only in speed. */
 enum { BF_DAS_LDS = 0, BF_DAS_GATHER = 1, BF_DAS_LDS_Z2 = 2 };
 
@@ -241,7 +244,7 @@ int bf_das(bf_plan plan, const void *e, float *out, double c, void *stream);
 /* bf_das for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and the same result bit for bit, but the partial images of a
- * channel-split launch (grids with fewer than 8192 wavefronts of points; see
+ * channel-split launch (grids with few workgroups; see
  * bf_plan_info.channel_groups) go to a static device array of
  * BF_DAS_NOALLOC_MAX_BYTES per GPU, which the library holds until the process
  * ends, instead of plan memory.  The call itself allocates nothing (the plan
@@ -249,9 +252,9 @@ int bf_das(bf_plan plan, const void *e, float *out, double c, void *stream);
  * GPU's array, so calls that overlap on one GPU (other streams, other host
  * threads) race; calls queued on one stream do not.  The current device must
  * be the plan's (BF_ERR_STATE otherwise).  BF_ERR_TOO_LARGE if the plan's
- * partial images exceed the array (the channel split keeps them below 8 MiB
+ * partial images exceed the array (the channel split keeps them within 32 MiB
  * for every plan).  Other errors as bf_das. */
-#define BF_DAS_NOALLOC_MAX_BYTES (8u << 20)
+#define BF_DAS_NOALLOC_MAX_BYTES (32u << 20)
 int bf_das_noalloc(bf_plan plan, const void *e, float *out, double c, void *stream);
 
 /* Decode fused into DAS (Sec. VII-C's decode -> beamform order in one

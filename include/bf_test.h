@@ -26,6 +26,11 @@ double bf_test_hann_poly(double u2);
  * depend on it.  BF_ERR_SHAPE for cap < 0. */
 int bf_test_set_stack_cap(bf_plan plan, int32_t cap);
 
+/* Restrict the mirror axes of a plan (bit 0: y, bit 1: x; before its first
+ * batched launch) and return the axes its frames then use, so that tests can
+ * compare mirrored launches with plain ones. */
+int bf_test_set_mirrors(bf_plan plan, int32_t allowed);
+
 #ifdef __cplusplus
 }
 #endif

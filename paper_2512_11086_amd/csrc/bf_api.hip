@@ -278,6 +278,7 @@ int Frame::init(const bf_params &src)
             nb = 48;   // trimmed to the LDS cap and staging rounds by lds_config
         }
     }
+    find_mirrors();
     sorted_tx = 1;
     for (int i = 1; i < n; ++i)
         if (tx_x[i] < tx_x[i - 1]) sorted_tx = 0;
@@ -308,8 +309,8 @@ int Frame::init(const bf_params &src)
     // partial-sum buffer of the adjoint, large enough for any tile: one entry
     // per 4-wavefront block (gather kernel) or per (LDS workgroup, channel
     // group); a box holds at least one wavefront, the slab order pads the
-    // boxes to whole groups of 8 depth slabs (at most 8x), and the channel
-    // split keeps groups x wavefronts below wavefronts + 8192
+    // boxes to whole groups of 8 depth slabs (at most 8x), and the adjoint's
+    // channel split keeps groups x wavefronts below wavefronts + 8192
     long max_waves = 0;
     for (int lx = 0; lx <= 6; ++lx)
         for (int ly = 0; ly + lx <= 6; ++ly) {
@@ -321,20 +322,18 @@ int Frame::init(const bf_params &src)
     max_blocks = 8 * (max_waves + 8192);
     d_partial = (double *)alloc((size_t)max_blocks * sizeof(double));
     {
-        // Eq. 3 in double precision at u^2 = k / (4 HANN_N): entry k holds the
-        // slope D_k = W_{k+1} - W_k and the base W_k - k D_k (with D_k as
-        // rounded), so that the weight at table coordinate x in [k, k + 1) is
-        // one FMA, base + x D_k
+        // Eq. 3 in double precision: entry k holds the chord of W over
+        // q HANN_N in [k - 1/2, k + 1/2] (q = 4 u^2 >= 0), its slope in q and,
+        // with the slope as rounded, its value at q = 0
         std::vector<float2> tab(HANN_N + 1);
-        std::vector<double> W(HANN_N + 1);
-        for (int k = 0; k <= HANN_N; ++k) {
-            const double u = sqrt(k / (4.0 * HANN_N));
-            const double cu = cos(M_PI * u);
-            W[k] = (k == HANN_N) ? 0.0 : cu * cu;
-        }
+        auto hann = [](double v) {          // W at q = v / HANN_N
+            const double cu = cos(M_PI * 0.5 * sqrt(v / HANN_N));
+            return cu * cu;
+        };
         for (int k = 0; k < HANN_N; ++k) {
-            const float d = (float)(W[k + 1] - W[k]);
-            tab[k] = make_float2((float)(W[k] - k * (double)d), d);
+            const double lo = std::max(k - 0.5, 0.0), hi = k + 0.5;
+            const float d = (float)((hann(hi) - hann(lo)) / (hi - lo) * HANN_N);
+            tab[k] = make_float2((float)(hann(lo) - lo / HANN_N * (double)d), d);
         }
         tab[HANN_N] = make_float2(0.f, 0.f);
         d_hann = (float2 *)alloc(tab.size() * sizeof(float2));
@@ -342,21 +341,10 @@ int Frame::init(const bf_params &src)
         hipError_t he = hipMemcpy(d_hann, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
         if (he != hipSuccess) return hip_fail(he, "upload of the Hann table");
     }
-    // Small grids give too few wavefronts to fill 256 CUs; split the channel
-    // sum over `groups` workgroup sets (>= 8192 wavefronts in flight) and add
-    // the partial images in a fixed order afterwards.
-    {
-        const long nvox = (long)grid.nx * grid.ny * grid.nz;
-        const long waves = (nvox + 63) / 64;
-        long G = (8192 + waves - 1) / waves;
-        const long gmax = p.n_ch / 4 > 1 ? p.n_ch / 4 : 1;
-        if (G > 16) G = 16;
-        if (G > gmax) G = gmax;
-        groups = (int)(G < 1 ? 1 : G);
-        if (groups > 1) {
-            d_part = (float *)alloc((size_t)groups * nvox * (p.iq ? 2 : 1) * sizeof(float));
-            if (!d_part) return fail(BF_ERR_HIP, "device allocation of partial images failed");
-        }
+    choose_groups();
+    if (groups > 1) {
+        d_part = (float *)alloc((size_t)groups * out_elems() * sizeof(float));
+        if (!d_part) return fail(BF_ERR_HIP, "device allocation of partial images failed");
     }
     if (!d_At || !d_colsum || !d_Hf || !d_tx_x || !d_rx_c || !d_partial)
         return fail(BF_ERR_HIP, "device allocation for plan tables failed");
@@ -372,6 +360,91 @@ int Frame::init(const bf_params &src)
             hipSuccess)
         return hip_fail(e, "upload of plan tables");
     return BF_OK;
+}
+
+// Channel groups: small grids give too few workgroups to fill 256 CUs, so the
+// channel sum is split over `groups` workgroup sets whose partial images are
+// added in a fixed order afterwards.
+//
+// adj_groups, the adjoint's split and the floor of the forward one, gives at
+// least 8192 wavefronts.  The forward split counts workgroups of the plan's
+// LDS launch, two per CU (512 slots):
+//  - Planes stage channels in chunks of JC rows, so a group of m chunks costs
+//    about m plus 1/4 for its setup; the m is taken whose rounds over the
+//    slots cost least (a round that is not full is partly hidden by the
+//    shallow boxes, which have fewer active rows).  256 x 256 points, 64
+//    traces (64 boxes): m = 1, 2, 4 run 131, 123, 155 us; 181 x 303 points,
+//    127 rows (57 boxes): 132, 127, 145 us, and 149 with the 10 groups of the
+//    floor.
+//  - Volumes aim at five workgroups per slot (HERCULES) or three (TPW, VLS,
+//    whose groups end in partial chunks): HERCULES 61 x 53 x 97 points from 24
+//    x 100 traces 764 us with 2 groups, 627 with 10; IQ 64 x 64 x 128 from 64 x
+//    64 traces 2 090 us with 1, 1 020 with 8.  A group keeps at least 192
+//    traces and two rows (eight in the separable modes): below that the
+//    partial images cost more than the balance gains.
+// The partial images stay within BF_DAS_NOALLOC_MAX_BYTES.
+void Frame::choose_groups()
+{
+    const long nvox = (long)grid.nx * grid.ny * grid.nz;
+    const long waves = (nvox + 63) / 64;
+    const long gmax = std::max(p.n_ch / 4, 1);
+    adj_groups = (int)std::max<long>(1, std::min<long>(std::min<long>((8192 + waves - 1) / waves, 16), gmax));
+    groups = adj_groups;
+    LdsCfg c;
+    if (variant == BF_DAS_GATHER || !lds_config(das_args(nullptr, nullptr, p.c), &c)) return;
+    const long boxes = (long)c.blocks_x * c.blocks_y * c.blocks_z;
+    const long slots = 512;
+    const long cap = std::max<long>(1, BF_DAS_NOALLOC_MAX_BYTES / (out_elems() * (long)sizeof(float)));
+    long G = 1;
+    if (p.mode == BF_FORCES_2D) {
+        double best = 1e300;
+        const int chunks = (p.n_ch + JC - 1) / JC;
+        for (int m = 1; m <= chunks; ++m) {
+            const long g = (chunks + m - 1) / m;
+            if (g > cap || g > gmax) continue;
+            const double r = (double)(boxes * g) / slots;
+            const double rounds = r <= 0.5 ? 0.7 : r <= 1.0 ? 1.0 : std::max(r, ceil(r) - 0.3);
+            if (rounds * (m + 0.25) < best) {
+                best = rounds * (m + 0.25);
+                G = g;
+            }
+        }
+        groups = (int)G;
+        return;
+    }
+    const bool herc = p.mode == BF_HERCULES_3D;
+    G = herc ? (5 * slots + boxes - 1) / boxes : (3 * slots + boxes / 2) / boxes;
+    G = std::min(G, (long)p.n_tx * p.n_ch / 192);
+    G = std::min(G, (long)p.n_ch / (herc ? 2 : 8));
+    groups = (int)std::max<long>(adj_groups, std::min<long>(std::min<long>(G, 16), cap));
+}
+
+// Axes along which a HERCULES geometry is its own mirror image about the
+// array centre: the grid's lines along the axis and the receivers on it (rows
+// for y, transmit columns for x) come in pairs of opposite sign, and the
+// other axes of the grid do not move along it.  A diverging source lies on the
+// centre, so its path is symmetric too.  Offsets are compared to 1e-9 of the
+// pitch (2e-9 sample at k = 20 samples per mm and 0.1 mm).
+void Frame::find_mirrors()
+{
+    mirrors = 0;
+    if (p.mode != BF_HERCULES_3D) return;
+    const double tol[2] = {1e-9 * p.pitch[0], 1e-9 * p.pitch[1]};
+    auto paired = [](const std::vector<int> &v, int n_elem) {
+        for (size_t i = 0; i < v.size(); ++i)
+            if (v[i] + v[v.size() - 1 - i] != n_elem - 1) return false;
+        return true;
+    };
+    auto small = [&](double v, int a) { return fabs(v) <= tol[a]; };
+    const double ext[3] = {(double)(grid.nx - 1), (double)(grid.ny - 1), (double)(grid.nz - 1)};
+    if (paired(ch, p.n_elem[1]) && small(2.0 * grid.org[1] + ext[1] * grid.ay[1], 1) &&
+        small(ext[0] * grid.ax[1], 1) && small(ext[2] * grid.az[1], 1) &&
+        small(ext[1] * grid.ay[0], 0) && small(ext[1] * grid.ay[2], 1))
+        mirrors |= 1;
+    if (paired(tx, p.n_elem[0]) && small(2.0 * grid.org[0] + ext[0] * grid.ax[0], 0) &&
+        small(ext[1] * grid.ay[0], 0) && small(ext[2] * grid.az[0], 0) &&
+        small(ext[0] * grid.ax[1], 1) && small(ext[0] * grid.ax[2], 0))
+        mirrors |= 2;
 }
 
 void Frame::set_tile(int lx_, int ly_, int lz_)
@@ -470,9 +543,33 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
     const bool sep = p.mode != BF_HERCULES_3D;   // separable: FORCES, TPW, VLS
     const int *bw = bw_adj ? bw_adj : this->bw;
     const int lx = a.lx, ly = a.ly, lz = a.lz;
-    // points per lane along z: two for the HERCULES real-data variant
-    const int zp = variant == BF_DAS_LDS_Z2 && z2_ok() ? 2 : 1;
-    const int tx = bw[0] << lx, ty = bw[1] << ly, tz = (bw[2] << lz) * zp;
+    const int tx = bw[0] << lx, ty = bw[1] << ly;
+    // Mirror points: a mirrored axis needs the boxes of its lower half only,
+    // each with twice the points.  The axes are taken that make the launch
+    // cheapest, counting a box as 1 plain, 1.45 mirrored along one axis and
+    // 2.4 along both (headline volume, us: 22 830 plain, 16 480 mirrored in y,
+    // 13 720 in x and y; its IQ counterpart with 64 x 64 traces 1 668, 1 132
+    // and 1 022): an axis of few boxes halves badly.  Nearest reads keep
+    // the unsplit position, which the mirror terms do not have.
+    cfg->mir = MIRROR_NONE;
+    cfg->ex = grid.nx;
+    cfg->ey = grid.ny;
+    if (!sep && adj == 0 && p.interp != BF_INTERP_NEAREST) {
+        auto boxes = [](int n, int t) { return (n + t - 1) / t; };
+        const double bx = boxes(grid.nx, tx), by = boxes(grid.ny, ty);
+        const double hx = boxes((grid.nx + 1) / 2, tx), hy = boxes((grid.ny + 1) / 2, ty);
+        const double cost[4] = {bx * by, 1.45 * bx * hy, 1.45 * hx * by, 2.4 * hx * hy};
+        for (int m = 1; m < 4; ++m)
+            if ((mirrors & m) == m && cost[m] < cost[cfg->mir]) cfg->mir = m;
+        if (cfg->mir & MIRROR_Y) cfg->ey = (grid.ny + 1) / 2;
+        if (cfg->mir & MIRROR_X) cfg->ex = (grid.nx + 1) / 2;
+    }
+    const int nm = mirror_copies(cfg->mir);
+    // points per lane along z: two for the real-data variant without mirror
+    // points (with them one: 13 720 against 14 620 us in x and y, and boxes
+    // half as deep balance better)
+    const int zp = variant == BF_DAS_LDS_Z2 && z2_ok() && nm == 1 ? 2 : 1;
+    const int tz = (bw[2] << lz) * zp;
     // VLS: the transmit path jumps at the virtual line's depth (converging
     // above it, diverging below), so no box may hold points of both sides:
     // the box grid is shifted along z to start a box where the side changes.
@@ -535,6 +632,8 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
     const int nthr = 64 * bw[0] * bw[1] * bw[2];
     const int unit = sep ? JC : 1;      // separable modes: JC rows per batch
     int nbb = std::max(nb - nb % unit, unit);
+    if (nm > 1)    // the windows of a copy fill one set; a lane describes one slot, 64 per batch
+        nbb = std::min(nbb, std::min(64 / nm, mirror_set_quads(nm) / (lmax * (p.iq ? 2 : 1))));
     const size_t lds_cap = lds_cap_bytes();
     const int nwaves = nthr / 64;
     // staging rounds per thread: the batch's quads (real data: pairs of
@@ -542,11 +641,11 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
     // kernels unroll
     const int max_rounds = stage_rounds(p.mode, p.iq != 0);
     const int per_trace = pairs ? lmax / 2 : lmax;
-    auto rounds = [&](int n) { return (n * per_trace + 64 * nwaves - 1) / (64 * nwaves); };
+    auto rounds = [&](int n) { return (nm * n * per_trace + 64 * nwaves - 1) / (64 * nwaves); };
     const int qs = p.iq ? 2 : 1;
     const bool staged = adj == 0 || (adj & 1);    // the RF gradient alone reads no data
     while (nbb >= unit && ((staged && rounds(nbb) > max_rounds) ||
-                           lds_bytes(p.n_tx, p.n_ch, nbb, lmax, qs, guard, adj, p.mode) > lds_cap))
+                           lds_bytes(p.n_tx, p.n_ch, nbb, lmax, qs, guard, adj, p.mode, nm) > lds_cap))
         nbb -= unit;
     if (nbb < unit || nthr > 1024) return false;
     cfg->bwx = bw[0];
@@ -562,8 +661,8 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
     cfg->zp = zp;
     cfg->z_off = z_off;
     cfg->guard = guard;
-    cfg->blocks_x = (grid.nx + tx - 1) / tx;
-    cfg->blocks_y = (grid.ny + ty - 1) / ty;
+    cfg->blocks_x = (cfg->ex + tx - 1) / tx;
+    cfg->blocks_y = (cfg->ey + ty - 1) / ty;
     cfg->blocks_z = (grid.nz + z_off + tz - 1) / tz;
     return true;
 }
@@ -680,6 +779,7 @@ int Frame::das_adjoint(const void *e, const float *grad_out, double c, float *gr
                        float *grad_c, int nf, hipStream_t s) const
 {
     DasArgs a = das_args(e, nullptr, c);
+    a.groups = adj_groups;
     a.grad_out = grad_out;
     a.grad_e = grad_e;
     const bool lds_ok = p.interp != BF_INTERP_NEAREST && variant != BF_DAS_GATHER;
@@ -851,8 +951,9 @@ int bf_plan_get_info(bf_plan plan, bf_plan_info *info)
         LdsCfg cfg;
         const bool lds = f.variant != BF_DAS_GATHER &&
                          f.lds_config(f.das_args(nullptr, nullptr, f.p.c), &cfg);
-        info->variant = lds ? (cfg.zp == 2 ? BF_DAS_LDS_Z2 : BF_DAS_LDS) : BF_DAS_GATHER;
-        info->nb = lds ? cfg.nb : f.nb;
+        const bool z2 = lds && (cfg.zp == 2 || (cfg.mir && f.variant == BF_DAS_LDS_Z2 && f.z2_ok()));
+        info->variant = lds ? (z2 ? BF_DAS_LDS_Z2 : BF_DAS_LDS) : BF_DAS_GATHER;
+        info->nb = lds ? cfg.nb * mirror_copies(cfg.mir) : f.nb;
     }
     info->block[0] = f.bw[0];
     info->block[1] = f.bw[1];
@@ -1013,6 +1114,21 @@ int bf_sharpness(const float *img, int64_t n_per_image, int32_t n_images, float 
 }
 
 double bf_test_hann_poly(double u2) { return (double)hann_u2((float)u2); }
+
+int bf_test_set_mirrors(bf_plan plan, int32_t allowed)
+{
+    g_err.clear();
+    int st = check_plan(plan);
+    if (st != BF_OK) return st;
+    int used = 0;
+    for (Frame *f : plan->frames) {
+        f->mirrors &= allowed;
+        LdsCfg cfg;
+        if (f->variant != BF_DAS_GATHER && f->lds_config(f->das_args(nullptr, nullptr, f->p.c), &cfg))
+            used |= cfg.mir;
+    }
+    return used;
+}
 
 int bf_test_set_stack_cap(bf_plan plan, int32_t cap)
 {

@@ -27,7 +27,7 @@ namespace bf {
 
 hipError_t launch_decode_persistent(const DecLaunch &p, hipStream_t s);
 hipError_t launch_das_persistent(const PersistentLaunch &p, hipStream_t s);
-int persistent_das_blocks(int mode, int et, int ip, int zp, int threads, size_t shm);
+int persistent_das_blocks(int mode, int et, int ip, int zp, int nm, int threads, size_t shm);
 hipError_t launch_fill(float *p, long n, float v, hipStream_t s);
 hipError_t launch_sum_groups(const DasArgs &a, hipStream_t s);
 
@@ -51,7 +51,7 @@ struct DasItem {
 };
 
 struct DasClass {
-    int mode, et, ip, zp, threads;
+    int mode, et, ip, zp, nm, threads;
     size_t shm = 0;
     std::vector<DasItem> items;
     int4 *d_items = nullptr;
@@ -135,8 +135,8 @@ static int build_batch(bf_plan plan)
             LdsCfg c;
             if (fr.variant == BF_DAS_GATHER || !fr.lds_config(a, &c)) continue;
             lds_ok[f] = 1;
-            key[f] = ((((long)fr.p.mode * 8 + fr.p.e_type) * 8 + fr.p.interp) * 4 + c.zp) * 2048 +
-                     64 * c.bwx * c.bwy * c.bwz;
+            key[f] = ((((long)fr.p.mode * 8 + fr.p.e_type) * 8 + fr.p.interp) * 4 + c.zp) * 8192 +
+                     2048 * mirror_copies(c.mir) / 2 + 64 * c.bwx * c.bwy * c.bwz;
             const long nblk = (long)c.blocks_x * c.blocks_y * c.blocks_z;
             bool found = false;
             for (auto &kb : cls_boxes)
@@ -172,7 +172,7 @@ static int build_batch(bf_plan plan)
             b->gather_frames.push_back(f);
             memset(&c, 0, sizeof c);
         } else if (groups[f] > 1 &&
-                   (long)c.blocks_x * c.blocks_y * c.blocks_z * fr.groups >= 2L * cus0) {
+                   (long)c.blocks_x * c.blocks_y * c.blocks_z * fr.adj_groups >= 2L * cus0) {
             // A frame of a class that would need the channel split, whose own
             // launch (the single-frame kernel with the frame's channel groups)
             // already gives two workgroups per CU: that launch, captured in
@@ -193,11 +193,12 @@ static int build_batch(bf_plan plan)
                 b->split_frames.push_back(f);
             }
             const int threads = 64 * c.bwx * c.bwy * c.bwz;
-            const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, 1, c.guard, 0, fr.p.mode);
+            const int nm = mirror_copies(c.mir);
+            const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, 1, c.guard, 0, fr.p.mode, nm);
             DasClass *cls = nullptr;
             for (DasClass &d : b->das)
                 if (d.mode == fr.p.mode && d.et == fr.p.e_type && d.ip == fr.p.interp &&
-                    d.zp == c.zp && d.threads == threads)
+                    d.zp == c.zp && d.nm == nm && d.threads == threads)
                     cls = &d;
             if (!cls) {
                 DasClass d;
@@ -205,6 +206,7 @@ static int build_batch(bf_plan plan)
                 d.et = fr.p.e_type;
                 d.ip = fr.p.interp;
                 d.zp = c.zp;
+                d.nm = nm;
                 d.threads = threads;
                 b->das.push_back(d);
                 cls = &b->das.back();
@@ -302,7 +304,7 @@ static int build_batch(bf_plan plan)
         if ((e = hipMemcpy(d.d_items, it.data(), sizeof(int4) * it.size(), hipMemcpyHostToDevice)) !=
             hipSuccess)
             return hip_fail(e, "batch item upload");
-        d.grid = std::min(d.n_items, persistent_das_blocks(d.mode, d.et, d.ip, d.zp, d.threads, d.shm));
+        d.grid = std::min(d.n_items, persistent_das_blocks(d.mode, d.et, d.ip, d.zp, d.nm, d.threads, d.shm));
     }
     for (int k = 0; k < RING; ++k) {
         if ((e = hipHostMalloc((void **)&b->h_stage[k], sizeof(void *) * 2 * F)) != hipSuccess)
@@ -366,6 +368,7 @@ static int enqueue(bf_plan plan, hipStream_t s)
         L.et = d.et;
         L.ip = d.ip;
         L.zp = d.zp;
+        L.nm = d.nm;
         L.grid = d.grid;
         L.threads = d.threads;
         L.shm = d.shm;
@@ -669,9 +672,11 @@ int bf_autotune(bf_plan plan, const char *cache_path)
             // A batch plan runs each kernel class (mode, type, interpolation,
             // points per lane, workgroup size) as one persistent launch: its
             // candidates keep the workgroup size, the points per lane and the
-            // LDS kernel, so that tuning one class does not split it into
+            // LDS kernel (and its mirror points), so that tuning one class does not split it into
             // separate launches that run one after the other.
             const int threads0 = saved[3] * saved[4] * saved[5];
+            LdsCfg cfg0;
+            const bool lds0 = f0->lds_config(f0->das_args(e_buf, o_buf, f0->p.c), &cfg0);
             for (const TileCand &t : cands) {
                 if (batch && (t.bwx * t.bwy * t.bwz != threads0 || t.variant != saved_variant))
                     continue;
@@ -684,6 +689,8 @@ int bf_autotune(bf_plan plan, const char *cache_path)
                 LdsCfg cfg;
                 if (t.variant != BF_DAS_GATHER &&
                     !f0->lds_config(f0->das_args(e_buf, o_buf, f0->p.c), &cfg))
+                    continue;
+                if (batch && lds0 && t.variant != BF_DAS_GATHER && mirror_copies(cfg.mir) != mirror_copies(cfg0.mir))
                     continue;
                 if (f0->das(e_buf, o_buf, f0->p.c, 0) != BF_OK) continue;   // warm-up
                 (void)hipEventRecord(t0, 0);

@@ -75,7 +75,7 @@ struct DasArgs {
     int groups;             // channel groups (blockIdx.y); > 1 writes partial images
     float *part;            // [groups][ny][nx][nz] partial images when groups > 1
     float *const *out_ref;  // if set, the output pointer is read from here (graph replay)
-    const float2 *hann_tab; // [HANN_N + 1] (base, slope) of W over u^2 in [0, 1/4]
+    const float2 *hann_tab; // [HANN_N + 1] (base, slope) of W over 4 u^2 in [0, 1]
     int cx;                 // IQ data: e, out and part hold (re, im) pairs
     float rot;              // IQ: fd / fs, revolutions of carrier phase per sample
     double rot_d;           // the same in FP64 (per-lane phase origin)
@@ -102,11 +102,11 @@ __host__ __device__ constexpr int stage_rounds(int mode, bool iq)
     return iq && (mode == MODE_TPW || mode == MODE_VLS) ? 3 : 2;
 }
 
-// Hann weight table: W(u) of Eq. 3 sampled at u^2 = k / (4 HANN_N), stored as
-// (W_k - k D_k, D_k) with D_k = W_{k+1} - W_k, so that linear interpolation
-// in u^2 at table coordinate x = 4 HANN_N u^2 is fma(x, D_k, W_k - k D_k)
-// for k = floor(x) (max error 1.2e-7, plus ~6e-8 for the rounded base);
-// entry HANN_N is (0, 0), so every u^2 >= 1/4 reads weight 0.
+// Hann weight table: W(u) of Eq. 3 over q = 4 u^2 in [0, 1], HANN_N steps.
+// Entry k serves q HANN_N in [k - 1/2, k + 1/2] (the nearest entry is taken,
+// see hann_weight) with the chord of W over that step: (base, slope), so the
+// weight is fma(q, slope, base) (max error 1.2e-7, plus ~6e-8 for the rounded
+// base); entry HANN_N is (0, 0), so every q >= 1 reads weight 0.
 constexpr int HANN_N = 2048;
 
 __device__ inline float *das_out(const DasArgs &a) { return a.out_ref ? *a.out_ref : a.out; }
@@ -137,7 +137,24 @@ struct LdsCfg {
                          // (VLS: no box straddles the virtual line's depth)
     int guard;           // zeroed sample intervals after the second window buffer
                          // (HERCULES: reads of lanes outside their aperture)
+    int ex, ey;          // grid columns and rows the boxes cover (a mirrored axis: its lower half)
+    int mir;             // MIRROR_*: the axis along which a lane also computes the mirror points
 };
+
+// Mirrored HERCULES launches (das_block, NM = 2 or 4): the aperture and the
+// grid are symmetric about the array centre along y, x or both, so the term of
+// a point p with trace (i, j) has the delay and the weight of p's mirror point
+// with the mirror trace (i, n_ch - 1 - j) or (n_tx - 1 - i, j).
+enum { MIRROR_NONE = 0, MIRROR_Y = 1, MIRROR_X = 2, MIRROR_XY = 3 };
+__host__ __device__ constexpr int mirror_copies(int mir)
+{
+    return mir == MIRROR_XY ? 4 : mir == MIRROR_NONE ? 1 : 2;
+}
+// Quads of one window set of a mirrored launch: copy m of a batch's windows
+// starts m sets after copy 0, a constant that the reads carry as their
+// immediate offset.  Two batches of NM sets fill what the 80 KiB of a
+// workgroup leave beside the tables (at n_tx, n_ch <= 256).
+__host__ __device__ constexpr int mirror_set_quads(int nm) { return nm == 4 ? 484 : 968; }
 
 // Workgroups of a single-frame LDS launch (box order xcd_slab_box): whole
 // groups of 8 depth slabs.
@@ -160,7 +177,7 @@ struct QueueSet {
 };
 
 struct PersistentLaunch {
-    int mode, et, ip, zp;
+    int mode, et, ip, zp, nm;
     int grid, threads;
     size_t shm;
     const FrameDas *frames;
@@ -213,6 +230,12 @@ __device__ inline float4 lds_read_f4(unsigned addr)
     const v4f v = *(lptr<v4f>)(size_t)addr;
     return make_float4(v.x, v.y, v.z, v.w);
 }
+__device__ inline float2 lds_read_f2(unsigned addr)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f v = *(lptr<v2f>)(size_t)addr;
+    return make_float2(v.x, v.y);
+}
 
 // Vector accesses through those views go element by element (the views do
 // not carry the vector types' constructors); the compiler merges them into
@@ -254,14 +277,21 @@ __device__ inline float phase_origin(const DasArgs &a, int nB)
 
 // IQ term: acc += w * v * exp(j 2 pi ph) with ph in revolutions.  The hardware
 // sine and cosine take revolutions; the argument is reduced to [0, 1) first.
-__device__ inline void rotate_acc(float2 v, float w, float ph, float2 &acc)
+__device__ inline float2 rotation(float w, float ph)
 {
     const float f = __builtin_amdgcn_fractf(ph);
-    const float wc = w * __builtin_amdgcn_cosf(f), ws = w * __builtin_amdgcn_sinf(f);
-    acc.x = fmaf(v.x, wc, acc.x);
-    acc.x = fmaf(-v.y, ws, acc.x);
-    acc.y = fmaf(v.x, ws, acc.y);
-    acc.y = fmaf(v.y, wc, acc.y);
+    return make_float2(w * __builtin_amdgcn_cosf(f), w * __builtin_amdgcn_sinf(f));
+}
+__device__ inline void rotate_add(float2 v, float2 r, float2 &acc)
+{
+    acc.x = fmaf(v.x, r.x, acc.x);
+    acc.x = fmaf(-v.y, r.y, acc.x);
+    acc.y = fmaf(v.x, r.y, acc.y);
+    acc.y = fmaf(v.y, r.x, acc.y);
+}
+__device__ inline void rotate_acc(float2 v, float w, float ph, float2 &acc)
+{
+    rotate_add(v, rotation(w, ph), acc);
 }
 
 // Per-lane state of one output point of a DAS wavefront tile.

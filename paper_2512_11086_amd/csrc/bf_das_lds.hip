@@ -7,14 +7,14 @@ namespace bf {
 
 hipError_t launch_sum_groups(const DasArgs &a, hipStream_t s);
 
-template <int MODE, int ET, int IP, int ZP>
+template <int MODE, int ET, int IP, int ZP, int NM>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WavesPerEu<MODE, ZP>::value)))
 void das_lds_kernel(DasArgs a, LdsCfg c)
 {
     extern __shared__ float4 smem[];
     const int blk = xcd_slab_box(c, blockIdx.x);
     if (blk < 0) return;
-    das_block<MODE, ET, IP, ZP>(a, c, blk, blockIdx.y, smem);
+    das_block<MODE, ET, IP, ZP, 0, NM>(a, c, blk, blockIdx.y, smem);
 }
 
 // Persistent form for a batch of frames: each workgroup pulls (frame, box,
@@ -27,7 +27,7 @@ void das_lds_kernel(DasArgs a, LdsCfg c)
 // trace windows in that XCD's L2.  A workgroup drains its home queue, then
 // takes what is left in the others, so uneven queues still balance.  Every
 // workgroup leaves after one failed pull per queue.
-template <int MODE, int ET, int IP, int ZP>
+template <int MODE, int ET, int IP, int ZP, int NM>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WavesPerEu<MODE, ZP>::value)))
 void das_persistent_kernel(const FrameDas *__restrict__ frames,
                                                               const int4 *__restrict__ items,
@@ -52,22 +52,32 @@ void das_persistent_kernel(const FrameDas *__restrict__ frames,
             const int grp = __builtin_amdgcn_readfirstlane(items[beg + item].z);
             DasArgs a = frames[fr].a;
             a.out = static_cast<float *>(out_ptrs[fr]);
-            das_block<MODE, ET, IP, ZP>(a, frames[fr].c, blk, grp, smem);
+            das_block<MODE, ET, IP, ZP, 0, NM>(a, frames[fr].c, blk, grp, smem);
             __syncthreads();
         }
     }
 }
 
 
+template <int MODE, int ET, int IP, int ZP, int NM>
+static hipError_t launch_persistent5(const PersistentLaunch &p, hipStream_t s)
+{
+    const void *fn = reinterpret_cast<const void *>(&das_persistent_kernel<MODE, ET, IP, ZP, NM>);
+    hipError_t e = allow_lds(fn, p.shm);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((das_persistent_kernel<MODE, ET, IP, ZP, NM>), dim3(p.grid), dim3(p.threads),
+                       p.shm, s, p.frames, p.items, p.queues, p.counters, p.out_ptrs);
+    return hipGetLastError();
+}
+
 template <int MODE, int ET, int IP, int ZP>
 static hipError_t launch_persistent4(const PersistentLaunch &p, hipStream_t s)
 {
-    const void *fn = reinterpret_cast<const void *>(&das_persistent_kernel<MODE, ET, IP, ZP>);
-    hipError_t e = allow_lds(fn, p.shm);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((das_persistent_kernel<MODE, ET, IP, ZP>), dim3(p.grid), dim3(p.threads),
-                       p.shm, s, p.frames, p.items, p.queues, p.counters, p.out_ptrs);
-    return hipGetLastError();
+    if constexpr (MODE == MODE_HERCULES && IP != IN_NEAREST && ZP == 1) {   // (mirror points: one depth)
+        if (p.nm == 4) return launch_persistent5<MODE, ET, IP, ZP, 4>(p, s);
+        if (p.nm == 2) return launch_persistent5<MODE, ET, IP, ZP, 2>(p, s);
+    }
+    return p.nm == 1 ? launch_persistent5<MODE, ET, IP, ZP, 1>(p, s) : hipErrorInvalidValue;
 }
 
 template <int MODE, int ET, int IP>
@@ -112,34 +122,46 @@ hipError_t launch_das_persistent(const PersistentLaunch &p, hipStream_t s)
 }
 
 // Workgroups of the persistent DAS kernel that fit on the device at once.
-int persistent_das_blocks(int mode, int et, int ip, int zp, int threads, size_t shm)
+int persistent_das_blocks(int mode, int et, int ip, int zp, int nm, int threads, size_t shm)
 {
     int dev = 0, cus = 0, per = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const void *fn = nullptr;
     if (mode == 0 && et == ET_F32 && ip == IN_CUBIC)
-        fn = zp == 2 ? reinterpret_cast<const void *>(&das_persistent_kernel<0, ET_F32, IN_CUBIC, 2>)
-                     : reinterpret_cast<const void *>(&das_persistent_kernel<0, ET_F32, IN_CUBIC, 1>);
+        fn = zp == 2 ? reinterpret_cast<const void *>(&das_persistent_kernel<0, ET_F32, IN_CUBIC, 2, 1>)
+                     : reinterpret_cast<const void *>(&das_persistent_kernel<0, ET_F32, IN_CUBIC, 1, 1>);
     else if (mode == 1 && et == ET_F32 && ip == IN_CUBIC)
-        fn = zp == 2 ? reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 2>)
-                     : reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 1>);
+        fn = zp == 2   ? reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 2, 1>)
+             : nm == 4 ? reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 1, 4>)
+             : nm == 2 ? reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 1, 2>)
+                       : reinterpret_cast<const void *>(&das_persistent_kernel<1, ET_F32, IN_CUBIC, 1, 1>);
     if (fn && allow_lds(fn, shm) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, shm) == hipSuccess && per > 0)
         return cus * per;
     return cus * 2;
 }
 
-template <int MODE, int ET, int IP, int ZP>
-static hipError_t launch_lds4(const DasArgs &a, const LdsCfg &c, size_t shm, hipStream_t s)
+template <int MODE, int ET, int IP, int ZP, int NM>
+static hipError_t launch_lds5(const DasArgs &a, const LdsCfg &c, size_t shm, hipStream_t s)
 {
     const int nthr = 64 * c.bwx * c.bwy * c.bwz;
     dim3 grid(xcd_slab_grid(c), a.groups);
     if (stage_pairs(ET == ET_CF32) && (c.lmax & 1)) return hipErrorInvalidValue;   // pairs of quads
-    hipError_t e = allow_lds(reinterpret_cast<const void *>(&das_lds_kernel<MODE, ET, IP, ZP>), shm);
+    hipError_t e = allow_lds(reinterpret_cast<const void *>(&das_lds_kernel<MODE, ET, IP, ZP, NM>), shm);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((das_lds_kernel<MODE, ET, IP, ZP>), grid, dim3(nthr), shm, s, a, c);
+    hipLaunchKernelGGL((das_lds_kernel<MODE, ET, IP, ZP, NM>), grid, dim3(nthr), shm, s, a, c);
     return hipGetLastError();
+}
+
+template <int MODE, int ET, int IP, int ZP>
+static hipError_t launch_lds4(const DasArgs &a, const LdsCfg &c, size_t shm, hipStream_t s)
+{
+    if constexpr (MODE == MODE_HERCULES && IP != IN_NEAREST && ZP == 1) {   // (mirror points: one depth)
+        if (c.mir == MIRROR_XY) return launch_lds5<MODE, ET, IP, ZP, 4>(a, c, shm, s);
+        if (c.mir != MIRROR_NONE) return launch_lds5<MODE, ET, IP, ZP, 2>(a, c, shm, s);
+    }
+    return c.mir == MIRROR_NONE ? launch_lds5<MODE, ET, IP, ZP, 1>(a, c, shm, s) : hipErrorInvalidValue;
 }
 
 template <int MODE, int ET, int IP>
@@ -179,14 +201,15 @@ static hipError_t launch_lds_et(const DasArgs &a, const LdsCfg &c, int et, int i
 // table (a.hf); the same LDS kernel with the decode in its staging.
 hipError_t launch_das_lds_fused(const DasArgs &a, const LdsCfg &c, int ip, hipStream_t s);
 
-size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode)
+size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
+                 int nm)
 {
     const bool stage = adj == 0 || (adj & 1);     // data windows staged
     // tx_x and rx_c (and the separable modes' path bounds: one more of each)
     const int tables = (mode == MODE_HERCULES ? 1 : 2) * (((n_tx + 3) & ~3) + ((n_ch + 3) & ~3));
     return (size_t)(tables + 2 * ((nb + 3) & ~3)) * 4 +
            (mode == MODE_HERCULES ? (size_t)HANN_TAB_PAD * 8 : 0) +
-           (stage ? (2 * (size_t)nb * lmax + guard) * qs * 16 : 0) +
+           (stage ? (2 * (size_t)(nm > 1 ? nm * mirror_set_quads(nm) : nb * lmax * qs) + guard * qs) * 16 : 0) +
            ((adj & 2) ? 2 * (size_t)nb * (lmax + 3) * 8 + 16 * 4 : 0);
 }
 
@@ -201,7 +224,8 @@ hipError_t launch_das_lds_fused(const DasArgs &a, const LdsCfg &c, int ip, hipSt
 hipError_t launch_das_lds(const DasArgs &a, const LdsCfg &c, int mode, int et, int ip,
                           hipStream_t s)
 {
-    const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, a.cx ? 2 : 1, c.guard, 0, mode);
+    const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, a.cx ? 2 : 1, c.guard, 0, mode,
+                                 mirror_copies(c.mir));
     hipError_t err;
     switch (mode) {
         case MODE_FORCES: err = launch_lds_et<MODE_FORCES>(a, c, et, ip, shm, s); break;

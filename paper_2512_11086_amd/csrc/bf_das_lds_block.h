@@ -14,6 +14,13 @@
 // beamformed (double-buffered LDS, one barrier per batch), and they read
 // contiguous runs along fast time.
 //
+// HERCULES volumes whose aperture and grid are symmetric about the array
+// centre give each lane the mirror images of its point (NM = 2 or 4, see
+// das_block): one delay and one weight serve all of them, which takes the
+// bound from VALU issue (21.5 instructions per active term) towards the LDS
+// reads (16 bytes per term): the 128 x 128 x 256 volume from 128 x 128 traces
+// runs 24.5 ms plain with two depth points, 13.2 ms with mirror points.
+//
 // HERCULES volumes with real data can give each lane two adjacent depth
 // points (ZP = 2): both share the lateral offset to the receiver, rho^2 and
 // the per-trace scalars of every term, and each wavefront's per-batch work
@@ -128,10 +135,18 @@ struct LaneL {
     bool valid;
     float x, y, z, z2, thr, wsc, fB;
     float zk, zk2;  // z / k and its square (k = fs / c): the HERCULES delay
-    float wtab;     // u^2 * 4 HANN_N = rho^2 * wtab (table coordinate)
+    float wtab;     // 4 u^2 = rho^2 * wtab (q of the Hann table)
     int nB;
     float ph0;      // IQ: carrier phase of sample position nB (revolutions)
 };
+
+// Grid extents the boxes of a launch cover: the whole grid, or the lower half
+// of a mirrored axis (NM > 1; the others read the grid's own sizes, which
+// keeps two scalar registers free).
+template <int NM>
+__device__ inline int ext_x(const DasArgs &a, const LdsCfg &c) { return NM > 1 ? c.ex : a.g.nx; }
+template <int NM>
+__device__ inline int ext_y(const DasArgs &a, const LdsCfg &c) { return NM > 1 ? c.ey : a.g.ny; }
 
 // Grid indices of point p (0 .. zp-1) of a lane: the lane's z tile index
 // times zp plus p, so a lane's points are adjacent along z.
@@ -148,20 +163,20 @@ __device__ inline void lane_point(const DasArgs &a, const LdsCfg &c, int bx, int
 }
 
 // nref (folded HERCULES reads): fB then holds B - nref in one FP32 rounding.
-template <int MODE>
+template <int MODE, int NM>
 __device__ inline LaneL lane_setup_l(const DasArgs &a, const LdsCfg &c, int bx, int by, int bz,
                                      int wave, int lane, int p, const int *nref = nullptr)
 {
     LaneL L;
     int ix, iy, iz;
     lane_point(a, c, bx, by, bz, wave, lane, p, &ix, &iy, &iz);
-    L.valid = ix < a.g.nx && iy < a.g.ny && iz >= 0 && iz < a.g.nz;
+    L.valid = ix < ext_x<NM>(a, c) && iy < ext_y<NM>(a, c) && iz >= 0 && iz < a.g.nz;
     // The terms read their windows without clamping the index, so every lane
     // takes the geometry of the nearest grid point of its box: its delay then
     // lies within the box's bounds (see hercules_term and the separable terms
     // of das_block)
-    ix = min(ix, a.g.nx - 1);
-    iy = min(iy, a.g.ny - 1);
+    ix = min(ix, ext_x<NM>(a, c) - 1);
+    iy = min(iy, ext_y<NM>(a, c) - 1);
     iz = min(max(iz, 0), a.g.nz - 1);
     const double px = a.g.org[0] + ix * a.g.ax[0] + iy * a.g.ay[0] + iz * a.g.az[0];
     const double py = a.g.org[1] + ix * a.g.ax[1] + iy * a.g.ay[1] + iz * a.g.az[1];
@@ -182,17 +197,18 @@ __device__ inline LaneL lane_setup_l(const DasArgs &a, const LdsCfg &c, int bx, 
     L.zk2 = L.zk * L.zk;
     L.thr = (L.valid && pz > 0.0) ? (a.f2 > 0.f ? L.z2 * 0.25f / a.f2 : __builtin_inff()) : -1.f;
     L.wsc = a.f2 > 0.f ? a.f2 / L.z2 : 0.f;
-    L.wtab = L.wsc * (4.f * HANN_N);
-    L.ph0 = phase_origin(a, L.nB);
+    L.wtab = L.wsc * 4.f;
+    L.ph0 = phase_origin(a, nref ? *nref : L.nB);
     return L;
 }
 
 // Array-frame bounding box of the workgroup's points (clamped to the grid).
+template <int NM>
 __device__ inline BoxGeom block_box(const DasArgs &a, const LdsCfg &c, int bx, int by, int bz)
 {
     const int tx = c.bwx << a.lx, ty = c.bwy << a.ly, tz = (c.bwz << a.lz) * c.zp;
     const int i0[3] = {bx * tx, by * ty, max(bz * tz - c.z_off, 0)};
-    const int i1[3] = {min(bx * tx + tx - 1, a.g.nx - 1), min(by * ty + ty - 1, a.g.ny - 1),
+    const int i1[3] = {min(bx * tx + tx - 1, ext_x<NM>(a, c) - 1), min(by * ty + ty - 1, ext_y<NM>(a, c) - 1),
                        min(bz * tz + tz - 1 - c.z_off, a.g.nz - 1)};
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
     for (int q = 0; q < 8; ++q) {
@@ -414,7 +430,8 @@ __device__ inline BatchDesc next_batch(const DasArgs &a, const LdsCfg &c, const 
 
 // Transmit i and channel row j of trace slot e = lane of batch d (j = -1: an
 // empty slot); *pad: a padding slot of the separable modes (geometry of row
-// j, no data).  Separable batches number their slots transmit-major.
+// j, no data).  Separable batches number their slots transmit-major.  HERCULES
+// with mirror points: e is the slot's column of the batch (trace_desc).
 template <int MODE>
 __device__ inline void slot_trace(const BatchDesc &d, int e, int *i, int *j, bool *pad)
 {
@@ -448,10 +465,10 @@ struct Staged {
 // Whether staging round q holds any slot of the batch (uniform: the
 // workgroup skips rounds past the last one, e.g. the second of the FORCES
 // plane's 16 windows of 128 quads, which its 1024 threads stage in one).
-template <bool PR>
+template <bool PR, int NM>
 __device__ inline bool stage_round_live(const LdsCfg &c, int q, int nwaves)
 {
-    const int slots = PR ? (c.nb * c.lmax) >> 1 : c.nb * c.lmax;
+    const int slots = PR ? (NM * c.nb * c.lmax) >> 1 : NM * c.nb * c.lmax;
     return q == 0 || q * nwaves * 64 < slots;
 }
 
@@ -459,7 +476,7 @@ __device__ inline bool stage_round_live(const LdsCfg &c, int q, int nwaves)
 // none.  PR: pairs, m even.  (g + 1/2) / lmax, and (2g + 1) / lmax for
 // pairs, are at least 1 / (2 lmax) away from an integer, far more than the
 // FP32 rounding of the product for g < 2^16.
-template <bool PR>
+template <bool PR, int NM>
 __device__ inline bool stage_slot(const LdsCfg &c, int q, int wave, int lane, int nwaves, int *e,
                                   int *m)
 {
@@ -468,7 +485,20 @@ __device__ inline bool stage_slot(const LdsCfg &c, int q, int wave, int lane, in
     const int ee = (int)(((float)g2 + (PR ? 1.f : 0.5f)) * c.inv_lmax);
     *e = ee;
     *m = g2 - ee * c.lmax;
-    return ee < c.nb;
+    return ee < NM * c.nb;
+}
+
+// Whether copy m of a point (or trace) of a mirrored launch is mirrored in y
+// (rows), in x (columns).
+template <int NM>
+__device__ inline bool mirrored_y(const LdsCfg &c, int m)
+{
+    return NM == 4 ? (m & 1) != 0 : NM == 2 && m && c.mir == MIRROR_Y;
+}
+template <int NM>
+__device__ inline bool mirrored_x(const LdsCfg &c, int m)
+{
+    return NM == 4 ? (m & 2) != 0 : NM == 2 && m && c.mir == MIRROR_X;
 }
 
 // Descriptor of trace slot `lane` of batch d (see TraceDesc).  s_lo: the
@@ -478,16 +508,19 @@ __device__ inline bool stage_slot(const LdsCfg &c, int q, int wave, int lane, in
 // s_lo holds the box's integer window-start parts A_i (transmits) and B_j
 // (rows) instead of the path bounds, and the trace's window starts at
 // A_i + B_j.
-template <int MODE, bool FOLD = false>
+// NM > 1 (mirror points): slot e is copy e % NM of column e / NM of the
+// batch; the mirror traces share the window start of the trace they mirror.
+template <int MODE, bool FOLD = false, int NM = 1>
 __device__ inline TraceDesc trace_desc(const DasArgs &a, const LdsCfg &c, const BoxGeom &b,
                                        const float *s_tx, const float *s_rx, const float *s_lo,
                                        int lo_rx, const BatchDesc &d, int lane)
 {
     TraceDesc t{0, 0.f, NO_DATA, 0};
-    if (lane < c.nb) {
+    if (lane < NM * c.nb) {
         int i, j;
         bool pad;
-        slot_trace<MODE>(d, lane, &i, &j, &pad);
+        const int m = lane % NM;
+        slot_trace<MODE>(d, lane / NM, &i, &j, &pad);
         if (j >= 0) {
             t.xi = s_tx[i];
             t.ti = i;
@@ -503,6 +536,8 @@ __device__ inline TraceDesc trace_desc(const DasArgs &a, const LdsCfg &c, const 
                 t.sw = t.w0;
                 // 24-bit products: traces < 2^18, samples <= 2^16 (plan
                 // limits), element offsets < 2^31
+                if (mirrored_y<NM>(c, m)) j = a.n_ch - 1 - j;
+                if (mirrored_x<NM>(c, m)) i = a.n_tx - 1 - i;
                 const unsigned tr = __umul24((unsigned)i, (unsigned)a.n_ch) + (unsigned)j;
                 t.off = (int)__umul24(tr, (unsigned)a.S) + t.w0;
             }
@@ -513,17 +548,20 @@ __device__ inline TraceDesc trace_desc(const DasArgs &a, const LdsCfg &c, const 
 
 // Issue the global loads of a batch's windows (taps n-1 .. n+2 of every quad;
 // real data: n-1 .. n+3 of every pair of quads n, n+1).
-template <int ET, int QM>
+template <int ET, int QM, int NM>
 __device__ inline void stage_load(const DasArgs &a, const LdsCfg &c, const TraceDesc &td,
                                   Staged<QM> &st, int wave, int lane, int nwaves)
 {
     constexpr bool PR = stage_pairs(ET == ET_CF32);
+    constexpr int QS = ET == ET_CF32 ? 2 : 1;
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
-        if (!stage_round_live<PR>(c, q, nwaves)) break;
+        if (!stage_round_live<PR, NM>(c, q, nwaves)) break;
         int e, m;
-        const bool on = stage_slot<PR>(c, q, wave, lane, nwaves, &e, &m);
-        st.dst[q] = on ? e * c.lmax + m : -1;
+        const bool on = stage_slot<PR, NM>(c, q, wave, lane, nwaves, &e, &m);
+        // first quad of the slot's window, counted in sample intervals (mirror
+        // copies: in the copy's window set)
+        st.dst[q] = on ? (e / NM) * c.lmax + m + (NM > 1 ? (e % NM) * (mirror_set_quads(NM) / QS) : 0) : -1;
         // window start and data offset of slot e, from lane e
         const int src = (e & 63) << 2;
         const int w0 = __builtin_amdgcn_ds_bpermute(src, td.sw);
@@ -660,25 +698,27 @@ __device__ inline void store_w0(const LdsCfg &c, const TraceDesc &td, int *w, in
 // The HERCULES forward reads' per-slot value (hercules_term, HF): the LDS
 // byte address of slot `lane`'s window in buffer `quads` less (w0 - nR)
 // quads (modulo 2^32: the terms add floor(s) * 16 back, and the sum is the
-// address of quad floor(s) + nR - w0 of the window).
+// address of quad floor(s) + nR - w0 of the window; QS quads per interval).
+template <int QS, int NM>
 __device__ inline void store_w0_addr(const LdsCfg &c, const TraceDesc &td, int *w, const float4 *quads,
                                      int nR, int wave, int lane)
 {
-    if (wave != 0 || lane >= c.nb) return;
-    w[lane] = (int)(lds_addr(quads + lane * c.lmax) + ((unsigned)(nR - td.w0) << 4));
+    if (wave != 0 || lane >= NM * c.nb || lane % NM) return;
+    w[lane / NM] = (int)(lds_addr(quads + (lane / NM) * c.lmax * QS) +
+                         ((unsigned)(nR - td.w0) << (QS == 2 ? 5 : 4)));
 }
 
 // Convert the loaded taps to coefficient quads and write them to one LDS
 // buffer.  QS = quads per sample interval (2 for IQ data: real part, then
 // imaginary part).
-template <int IP, int QS, int QM, bool DQ>
+template <int IP, int QS, int QM, bool DQ, int NM>
 __device__ inline void stage_store(const LdsCfg &c, const Staged<QM> &st, float4 *quads, int wave,
                                    int lane, int nwaves)
 {
     constexpr bool PR = stage_pairs(QS == 2);
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
-        if (!stage_round_live<PR>(c, q, nwaves)) break;
+        if (!stage_round_live<PR, NM>(c, q, nwaves)) break;
         if (st.dst[q] >= 0) {
             const float *t = st.p[q];
             float4 *dst = quads + st.dst[q] * QS;
@@ -785,34 +825,107 @@ __device__ inline void flush_grad_e(const DasArgs &a, const LdsCfg &c, unsigned 
     }
 }
 
+// Hann weight of q = rho^2 wtab from the LDS table whose byte address less
+// the bits of 4096.0 (times the entry size) is `hann`: q saturates to [0, 1] in
+// its product (clamp modifier), 4096 + q has a unit of 1 / HANN_N in its last
+// place, so its bits number the nearest entry, and one shift-add gives the
+// entry's address: 4 instructions with the weight's FMA, 5 with a conversion
+// and a minimum (headline volume without mirror points 24.5 -> 23.5 ms).
+static_assert(HANN_N == 2048, "the unit of 4096.0 is 1 / HANN_N");
+__device__ inline unsigned hann_base(const float2 *tab)
+{
+    return lds_addr(tab) - (__float_as_uint(4096.f) << 3);
+}
+__device__ inline float2 hann_entry(unsigned hann, float q)
+{
+    return lds_read_f2((__float_as_uint(q + 4096.f) << 3) + hann);
+}
+
 // One HERCULES trace for the lane's ZP points: receiver at lateral offset
 // (x - xi, dy) from all of them (same x, y), trace window `win` starting at
 // sample interval w0 (passed negated, uniform).  The excess receive path in
 // samples, k rho^2 / (d + z), is evaluated as rho^2 / (d/k + z/k) with
 // d/k = sqrt(rho^2 / k^2 + (z/k)^2): the scale k is folded into the lane
 // constants (ik2 = 1 / k^2).
-// HF (real-data forward reads, cubic or linear): the lanes' fB hold
+// HF (forward reads, cubic or linear): the lanes' fB hold
 // fB + nB - nR for the box's reference sample nR, and neg_w0 carries the
-// LDS byte address of the trace's window less (w0 - nR) quads, so a read's
-// address is floor(s) * 16 plus that value: one shift-add per point.
-template <int ET, int IP, int ZP, int ADJ, bool HF = false>
+// LDS byte address of the trace's window less (w0 - nR) intervals, so a read's
+// address is floor(s) * 16 (IQ: 32) plus that value: one shift-add per point.
+// NM > 1: the point's mirror points take the same delay and weight with the
+// mirror traces, whose windows lie a constant number of sets further
+// (acc[m ZP + p]).
+template <int ET, int IP, int ZP, int ADJ, bool HF = false, int NM = 1>
 __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, int lmax,
-                                     const float2 *hann, float dy2, float ik2, float rot, float xi,
-                                     int neg_w0, float2 (&acc)[ZP],   // neg_w0: from LDS
+                                     unsigned hann, float dy2, float ik2, float rot, float xi,
+                                     int neg_w0, float2 (&acc)[ZP * NM],   // neg_w0: from LDS
                                      unsigned long long *gwin, const float (&G)[ZP])
 {
-    static_assert(!HF || (ET != ET_CF32 && ADJ == 0 && IP != IN_NEAREST),
-                  "folded reads: real-data forward, cubic or linear");
+    static_assert(!HF || (ADJ == 0 && IP != IN_NEAREST), "folded reads: forward, cubic or linear");
+    static_assert(NM == 1 || HF, "mirror points: folded reads");
     const float dx = L[0].x - xi;
     const float rho2 = fmaf(dx, dx, dy2);
+    if constexpr (HF) {
+        // Up to four 16-byte reads (and their points' Hann entries) are issued
+        // together before the first is used: a scheduling barrier keeps the
+        // compiler from pairing each read with its own wait, which serialized
+        // a wavefront on the latency of every read.
+        constexpr unsigned MS = mirror_set_quads(NM) * 16;
+        constexpr int QS = ET == ET_CF32 ? 2 : 1;
+        constexpr int MG = NM * QS <= 4 ? NM : 4 / QS;        // copies per group of reads
+        constexpr int PG = 1;
+#pragma unroll
+        for (int p0 = 0; p0 < ZP; p0 += PG) {
+            float s[PG], xw[PG];
+            float2 h[PG], r[PG];
+            unsigned ad[PG];
+            float4 q[PG * MG * QS];
+#pragma unroll
+            for (int m0 = 0; m0 < NM; m0 += MG) {
+#pragma unroll
+                for (int u = 0; u < PG; ++u) {
+                    const LaneL &l = L[p0 + u];
+                    if (m0 == 0) {
+                        const float dk = __builtin_amdgcn_sqrtf(fmaf(rho2, ik2, l.zk2));
+                        s[u] = fmaf(rho2, __builtin_amdgcn_rcpf(dk + l.zk), l.fB);
+                        xw[u] = __builtin_amdgcn_fmed3f(rho2 * l.wtab, 0.f, 1.f);
+                        h[u] = hann_entry(hann, xw[u]);
+                        ad[u] = ((unsigned)cvt_flr(s[u]) << (QS == 2 ? 5 : 4)) + (unsigned)neg_w0;
+                    }
+#pragma unroll
+                    for (int m = 0; m < MG; ++m)
+#pragma unroll
+                        for (int c = 0; c < QS; ++c)
+                            q[(u * MG + m) * QS + c] = lds_read_f4(ad[u] + (m0 + m) * MS + 16 * c);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < PG; ++u) {
+                    const float t = __builtin_amdgcn_fractf(s[u]);
+                    if (m0 == 0) {
+                        r[u].x = fmaf(xw[u], h[u].y, h[u].x);
+                        if constexpr (QS == 2) r[u] = rotation(r[u].x, fmaf(rot, s[u], L[p0 + u].ph0));
+                    }
+#pragma unroll
+                    for (int m = 0; m < MG; ++m) {
+                        float2 &o = acc[(m0 + m) * ZP + p0 + u];
+                        const float4 *v = q + (u * MG + m) * QS;
+                        if constexpr (QS == 2)
+                            rotate_add(make_float2(eval_quad<IP>(v[0], t), eval_quad<IP>(v[1], t)), r[u], o);
+                        else
+                            o.x = fmaf(r[u].x, eval_quad<IP>(v[0], t), o.x);
+                    }
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int p = 0; p < ZP; ++p) {
         const float dk = __builtin_amdgcn_sqrtf(fmaf(rho2, ik2, L[p].zk2));
         const float s = fmaf(rho2, __builtin_amdgcn_rcpf(dk + L[p].zk), L[p].fB);
-        const int li = HF ? 0 : add3_vvv(cvt_flr(s), L[p].nB, neg_w0);
-        // Hann weight from the LDS table; u^2 >= 1/4 lands on the (0, 0) entry
-        const float xw = rho2 * L[p].wtab;
-        const float2 h = hann[min((unsigned)cvt_flr(xw), (unsigned)HANN_N)];
+        const int li = add3_vvv(cvt_flr(s), L[p].nB, neg_w0);
+        const float xw = __builtin_amdgcn_fmed3f(rho2 * L[p].wtab, 0.f, 1.f);
+        const float2 h = hann_entry(hann, xw);
         const float w = fmaf(xw, h.y, h.x);
         // no clamp: li lies in [-1, lmax + guard) for every lane (its
         // geometry is inside the box); -1 reads the finite LDS word before the
@@ -821,7 +934,7 @@ __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, in
         const float t = __builtin_amdgcn_fractf(s);
         if constexpr (ET == ET_CF32) {
             const float2 v = make_float2(eval_quad<IP>(win[2 * li], t), eval_quad<IP>(win[2 * li + 1], t));
-            rotate_acc(v, w, fmaf(rot, s, L[p].ph0), acc[p]);
+            rotate_add(v, rotation(w, fmaf(rot, s, L[p].ph0)), acc[p]);
         } else if constexpr (ADJ != 0) {
             if constexpr ((ADJ & 1) != 0) {
                 // dL/dc: sums of w v'(s) and w v'(s) s (derivative quads)
@@ -831,10 +944,6 @@ __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, in
             }
             if constexpr ((ADJ & 2) != 0)   // RF gradient (active lanes lie inside the window)
                 scatter_taps<IP>(gwin, clamp0_i32(li, lmax - 1), G[p] * w, t);
-        } else if constexpr (HF) {
-            const unsigned ad = ((unsigned)cvt_flr(s) << 4) + (unsigned)neg_w0;
-            const float v = eval_quad<IP>(lds_read_f4(ad), t);
-            acc[p].x = fmaf(w, v, acc[p].x);
         } else {
             const float v = eval_quad<IP>(win[li], t);
             acc[p].x = fmaf(w, v, acc[p].x);
@@ -853,7 +962,12 @@ __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, in
 // in 64-bit fixed point, scaled by the box's largest |G| (two sets of
 // windows, one per batch buffer); a batch's windows go to grad_e while the
 // next batch is beamformed.  Without bit 1 no data are staged.
-template <int MODE, int ET, int IP, int ZP, int ADJ = 0>
+// NM > 1 (HERCULES forward reads, c.mir set): the workgroup also computes the
+// mirror images of its box, from the mirror traces staged beside its own.  The
+// delay and the weight of a term serve all NM points: one square root,
+// reciprocal, Hann entry and window address for NM terms; each further term
+// is one 16-byte read and four FMAs.
+template <int MODE, int ET, int IP, int ZP, int ADJ = 0, int NM = 1>
 __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int grp,
                                  float4 *smem)
 {
@@ -894,10 +1008,11 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     // sample choice is an integer decision that extra rounding would move at
     // near ties.
     constexpr bool FOLD = SEP && ADJ == 0 && ET != ET_CF32 && IP != IN_NEAREST;
-    // HERCULES forward reads on real data fold the lane's integer sample nB,
+    // HERCULES forward reads fold the lane's integer sample nB,
     // less a box reference nR, into its FP32 position (hercules_term, HF);
     // nearest reads keep the unsplit position, as above
-    constexpr bool HF = MODE == MODE_HERCULES && ADJ == 0 && ET != ET_CF32 && IP != IN_NEAREST;
+    constexpr bool HF = MODE == MODE_HERCULES && ADJ == 0 && IP != IN_NEAREST;
+    static_assert(NM == 1 || HF, "mirror points: HERCULES forward, cubic or linear");
     const int hc = FOLD ? c.lmax >> 2 : 0;
     const int ntx4 = (a.n_tx + 3) & ~3, nch4 = (a.n_ch + 3) & ~3;
     float *s_tx = reinterpret_cast<float *>(smem);
@@ -909,7 +1024,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     float2 *s_hann = reinterpret_cast<float2 *>(s_w0 + 2 * w0_stride);
     float4 *bufbase = reinterpret_cast<float4 *>(s_hann + (MODE == MODE_HERCULES ? HANN_TAB_PAD : 0));
     constexpr int QS = ET == ET_CF32 ? 2 : 1;     // quads per sample interval
-    const int buf_quads = STAGE ? c.nb * c.lmax * QS : 0;
+    const int buf_quads = !STAGE ? 0 : NM > 1 ? NM * mirror_set_quads(NM) : c.nb * c.lmax * QS;
     float4 *q0 = bufbase, *q1 = bufbase + buf_quads;
     // RF gradient: two sets of nb accumulation windows of lmax + 3 fixed-point
     // entries, then the wavefronts' maxima of |G|
@@ -924,14 +1039,15 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
         for (int t = tid; t < HANN_TAB_PAD; t += nthr)
             s_hann[t] = t <= HANN_N ? load_f2(a.hann_tab, t) : make_float2(0.f, 0.f);
     if constexpr (STAGE)   // finite data wherever an unclamped read can land
-        for (int t = tid; t < buf_quads + c.guard * QS; t += nthr) q1[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int t = tid - (NM > 1 ? buf_quads : 0); t < buf_quads + c.guard * QS; t += nthr)
+            q1[t] = make_float4(0.f, 0.f, 0.f, 0.f);
     if constexpr (GE)
         for (int t = tid; t < 2 * c.nb * lw; t += nthr) accw0[t] = 0ull;
 
     const int bz = blk % c.blocks_z;
     const int bx = (blk / c.blocks_z) % c.blocks_x;
     const int by = blk / (c.blocks_z * c.blocks_x);
-    const BoxGeom box = block_box(a, c, bx, by, bz);
+    const BoxGeom box = block_box<NM>(a, c, bx, by, bz);
     if constexpr (SEP) {   // the box's path bounds (read after the barrier below)
         const float zb = box.kf * fmaxf(box.zmin, 0.f);
         for (int t = tid; t < a.n_tx; t += nthr) {
@@ -951,7 +1067,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     const int nR = HF ? (int)floorf(fmaf(box.txlo + fmaxf(box.zmax, 0.f), box.kf, -box.t0f)) : 0;
     LaneL Lp[ZP];
 #pragma unroll
-    for (int p = 0; p < ZP; ++p) Lp[p] = lane_setup_l<MODE>(a, c, bx, by, bz, wave, lane, p, HF ? &nR : nullptr);
+    for (int p = 0; p < ZP; ++p) Lp[p] = lane_setup_l<MODE, NM>(a, c, bx, by, bz, wave, lane, p, HF ? &nR : nullptr);
     const LaneL &L = Lp[0];
     // largest rho^2 bound of the receive aperture over the lane's points
     float thr_l = Lp[0].thr;
@@ -960,9 +1076,9 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     const float kf = (float)a.k;
     const float ik2 = uniform_f((float)(1.0 / (a.k * a.k)));
     const float rot = a.rot;
-    float2 acc[ZP];
+    float2 acc[ZP * NM];
 #pragma unroll
-    for (int p = 0; p < ZP; ++p) acc[p] = make_float2(0.f, 0.f);
+    for (int p = 0; p < ZP * NM; ++p) acc[p] = make_float2(0.f, 0.f);
     // G(p) of the lane's points (RF gradient; 0 outside the grid and at z <= 0,
     // where the image is 0)
     float Gv[ZP];
@@ -1012,13 +1128,13 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     Staged<QM> st;
     TraceDesc td = {0, 0.f, NO_DATA, 0};   // descriptors of the current batch
     if (cur.valid) {
-        td = trace_desc<MODE, FOLD>(a, c, box, s_tx, s_rx, s_lo, ntx4, cur, lane);
+        td = trace_desc<MODE, FOLD, NM>(a, c, box, s_tx, s_rx, s_lo, ntx4, cur, lane);
         if constexpr (STAGE) {
-            stage_load<ET, QM>(a, c, td, st, wave, lane, nwaves);
-            stage_store<IP, QS, QM, GC>(c, st, q0, wave, lane, nwaves);
+            stage_load<ET, QM, NM>(a, c, td, st, wave, lane, nwaves);
+            stage_store<IP, QS, QM, GC, NM>(c, st, q0, wave, lane, nwaves);
         }
         if constexpr (HF)
-            store_w0_addr(c, td, s_w0, q0, nR, wave, lane);
+            store_w0_addr<QS, NM>(c, td, s_w0, q0, nR, wave, lane);
         else if constexpr (!FOLD)
             store_w0(c, td, s_w0, wave, lane);
     }
@@ -1042,8 +1158,8 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
         BatchDesc nxt = next_batch<MODE>(a, c, box, s_tx, s_rx, it);
         TraceDesc td_n = {0, 0.f, NO_DATA, 0};
         if (nxt.valid) {
-            td_n = trace_desc<MODE, FOLD>(a, c, box, s_tx, s_rx, s_lo, ntx4, nxt, lane);
-            if constexpr (STAGE) stage_load<ET, QM>(a, c, td_n, st, wave, lane, nwaves);
+            td_n = trace_desc<MODE, FOLD, NM>(a, c, box, s_tx, s_rx, s_lo, ntx4, nxt, lane);
+            if constexpr (STAGE) stage_load<ET, QM, NM>(a, c, td_n, st, wave, lane, nwaves);
         }
         // the previous batch's gradient windows (complete since the last barrier)
         if constexpr (GE)
@@ -1065,34 +1181,35 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
             // traces inside the union of this wavefront's receive apertures
             // (a contiguous run: the columns are sorted within a batch), in
             // pairs whose LDS reads overlap, then an odd last one
-            uint64_t mask = __ballot(lane < cur.cnt && mine.xi >= wlo && mine.xi <= whi);
+            uint64_t mask = __ballot(lane < NM * cur.cnt && lane % NM == 0 && mine.xi >= wlo && mine.xi <= whi);
             // per trace: the column position from the read-only table through
             // the scalar cache (uniform index) and the negated window start
             // from LDS -- no lane broadcasts (their SGPR results stall the wave)
+            const unsigned hann = hann_base(s_hann);
             const cptr<float> txcol = as_const(a.tx_x) + cur.i0;
             const int *wst = s_w0 + (bi & 1) * w0_stride;
             if constexpr (ZP == 2) {
                 // one trace per step already gives two independent terms
                 while (mask) {
-                    const int e1 = __builtin_ctzll(mask);
+                    const int e1 = __builtin_ctzll(mask) / NM;
                     mask &= mask - 1;
-                    hercules_term<ET, IP, ZP, ADJ, HF>(Lp, quads + e1 * c.lmax * QS, c.lmax, s_hann, dy2,
+                    hercules_term<ET, IP, ZP, ADJ, HF, NM>(Lp, quads + e1 * c.lmax * QS, c.lmax, hann, dy2,
                                               ik2, rot, txcol[e1], wst[e1], acc, accw + e1 * lw, Gv);
                 }
             }
             while (mask & (mask - 1)) {
-                const int e1 = __builtin_ctzll(mask);
+                const int e1 = __builtin_ctzll(mask) / NM;
                 mask &= mask - 1;
-                const int e2 = __builtin_ctzll(mask);
+                const int e2 = __builtin_ctzll(mask) / NM;
                 mask &= mask - 1;
-                hercules_term<ET, IP, ZP, ADJ, HF>(Lp, quads + e1 * c.lmax * QS, c.lmax, s_hann, dy2, ik2,
+                hercules_term<ET, IP, ZP, ADJ, HF, NM>(Lp, quads + e1 * c.lmax * QS, c.lmax, hann, dy2, ik2,
                                           rot, txcol[e1], wst[e1], acc, accw + e1 * lw, Gv);
-                hercules_term<ET, IP, ZP, ADJ, HF>(Lp, quads + e2 * c.lmax * QS, c.lmax, s_hann, dy2, ik2,
+                hercules_term<ET, IP, ZP, ADJ, HF, NM>(Lp, quads + e2 * c.lmax * QS, c.lmax, hann, dy2, ik2,
                                           rot, txcol[e2], wst[e2], acc, accw + e2 * lw, Gv);
             }
             if (mask) {
-                const int e1 = __builtin_ctzll(mask);
-                hercules_term<ET, IP, ZP, ADJ, HF>(Lp, quads + e1 * c.lmax * QS, c.lmax, s_hann, dy2, ik2,
+                const int e1 = __builtin_ctzll(mask) / NM;
+                hercules_term<ET, IP, ZP, ADJ, HF, NM>(Lp, quads + e1 * c.lmax * QS, c.lmax, hann, dy2, ik2,
                                           rot, txcol[e1], wst[e1], acc, accw + e1 * lw, Gv);
             }
         } else {
@@ -1195,7 +1312,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
                             const float t = __builtin_amdgcn_fractf(sq);
                             const float2 v = make_float2(eval_quad<IP>(win[2 * li], t),
                                                          eval_quad<IP>(win[2 * li + 1], t));
-                            rotate_acc(v, aj[q][p], fmaf(rot, sq, Lp[p].ph0), acc[p]);
+                            rotate_add(v, rotation(aj[q][p], fmaf(rot, sq, Lp[p].ph0)), acc[p]);
                         } else if constexpr (ADJ != 0) {
                             // the RF gradient's scatter stays inside the window;
                             // dL/dc alone reads unclamped, as the forward terms do
@@ -1220,9 +1337,9 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
         }
 
         if (!nxt.valid) break;
-        if constexpr (STAGE) stage_store<IP, QS, QM, GC>(c, st, ((bi + 1) & 1) ? q1 : q0, wave, lane, nwaves);
+        if constexpr (STAGE) stage_store<IP, QS, QM, GC, NM>(c, st, ((bi + 1) & 1) ? q1 : q0, wave, lane, nwaves);
         if constexpr (HF)
-            store_w0_addr(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride, ((bi + 1) & 1) ? q1 : q0, nR, wave,
+            store_w0_addr<QS, NM>(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride, ((bi + 1) & 1) ? q1 : q0, nR, wave,
                           lane);
         else if constexpr (!FOLD)
             store_w0(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride, wave, lane);
@@ -1273,14 +1390,21 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     for (int p = 0; p < ZP; ++p) {
         int ix, iy, iz;
         lane_point(a, c, bx, by, bz, wave, lane_e, p, &ix, &iy, &iz);
-        if (ix < a.g.nx && iy < a.g.ny && iz >= 0 && iz < a.g.nz) {
-            const long idx = ((long)iy * a.g.nx + ix) * a.g.nz + iz;
+        if (ix < ext_x<NM>(a, c) && iy < ext_y<NM>(a, c) && iz >= 0 && iz < a.g.nz) {
             const double pz = a.g.org[2] + ix * a.g.ax[2] + iy * a.g.ay[2] + iz * a.g.az[2];
-            const float2 v = pz > 0.0 ? acc[p] : make_float2(0.f, 0.f);
-            if constexpr (ET == ET_CF32)
-                store_f2(reinterpret_cast<float2 *>(dst), idx, v);
-            else
-                as_global_mut(dst)[idx] = v.x;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int jx = mirrored_x<NM>(c, m) ? a.g.nx - 1 - ix : ix;
+                const int jy = mirrored_y<NM>(c, m) ? a.g.ny - 1 - iy : iy;
+                // (the middle line of an odd axis is its own mirror image)
+                if ((mirrored_x<NM>(c, m) && jx == ix) || (mirrored_y<NM>(c, m) && jy == iy)) continue;
+                const long idx = ((long)jy * a.g.nx + jx) * a.g.nz + iz;
+                const float2 v = pz > 0.0 ? acc[m * ZP + p] : make_float2(0.f, 0.f);
+                if constexpr (ET == ET_CF32)
+                    store_f2(reinterpret_cast<float2 *>(dst), idx, v);
+                else
+                    as_global_mut(dst)[idx] = v.x;
+            }
         }
     }
 }
@@ -1325,6 +1449,7 @@ static inline hipError_t allow_lds(const void *fn, size_t shm)
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
 }
 
-size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode);
+size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
+                 int nm = 1);
 
 }  // namespace bf

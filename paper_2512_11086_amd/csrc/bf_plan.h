@@ -27,11 +27,13 @@ struct Frame {
     int bw[3] = {4, 4, 1};       // wavefront tiles per LDS workgroup (x, y, z)
     int nb = 16;                 // traces per staged batch
     int variant = 0;             // BF_DAS_LDS, BF_DAS_GATHER or BF_DAS_LDS_Z2
+    int mirrors = 0;             // axes of mirror symmetry (bit 0: y, bit 1: x; find_mirrors)
     int sorted_tx = 0;           // transmit columns ascending
     int uniform_tx = 0;          // transmit columns equally spaced (ascending)
     float tx_x0 = 0.f, tx_inv_dx = 0.f;
     double tpw_smax = 0.0;       // TPW: largest |sin| of the transmit angles
     int groups = 1;              // channel groups of the DAS launch (small grids)
+    int adj_groups = 1;          // channel groups of the adjoint launches
     int stack_cap = 0;           // frames per adjoint launch of a stack (0: no cap)
     float *d_part = nullptr;     // [groups][points] partial images
     float2 *d_hann = nullptr;    // Hann weight table (HANN_N + 1 entries)
@@ -50,6 +52,8 @@ struct Frame {
     void *alloc(size_t bytes);
     int init(const bf_params &src);
     void set_tile(int lx, int ly, int lz);
+    void find_mirrors();
+    void choose_groups();
     int64_t e_elems() const;
     int64_t out_elems() const;
     int das_et() const;          // element type of the DAS kernels (ET_CF32 for IQ plans)
@@ -76,7 +80,8 @@ hipError_t launch_das(const DasArgs &a, int mode, int et, int ip, hipStream_t s)
 hipError_t launch_das_lds(const DasArgs &a, const LdsCfg &c, int mode, int et, int ip,
                           hipStream_t s);
 hipError_t launch_das_lds_fused(const DasArgs &a, const LdsCfg &c, int ip, hipStream_t s);
-size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode);
+size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
+                 int nm = 1);
 hipError_t launch_das_lds_adjoint(const DasArgs &a, const LdsCfg &c, int mode, int ip,
                                   float *grad_c, hipStream_t s, int n_frames = 1);
 

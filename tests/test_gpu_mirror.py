@@ -1,0 +1,145 @@
+"""HERCULES launches with mirror points (a symmetric aperture and grid) against
+the FP64 oracle and against the plain launches of the same plan.
+
+The mirror of a point shares its delay and weight, so a mirrored launch has
+the plain launch's FP32 position rounding: both are held to the 1e-5 relative
+L2 of the DAS tests.  Geometries that are not their own mirror image (an
+offset grid, a lopsided transmit subset or channel map, a sheared grid) must
+take the plain launch.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2512_11086_amd as bfm
+import synth
+from paper_2512_11086_amd import _lib
+from synth.configs import MM, describe
+from tests.helpers import rel_l2
+
+pytestmark = pytest.mark.gpu
+TOL_L2 = 1e-5
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _desc(dims, n=24, S=700, **kw):
+    half = 0.1 * MM * n
+    args = dict(t0=1e-6, f_number=1.0, interp="cubic")
+    args.update(kw)
+    return describe("hercules", (n, n), (0.2 * MM, 0.2 * MM), n, n, S, 20e6, 5e6, dims,
+                    (-half, -half, 3 * MM), (half, half, 16 * MM), **args)
+
+
+def _data(desc, iq=False, seed=5):
+    shape = (desc["n_tx"], desc["n_ch"], desc["n_samples"]) + ((2,) if iq else ())
+    return np.random.default_rng(seed).standard_normal(shape).astype(np.float32)
+
+
+def _both(torch, desc, e, axes, e_type="f32"):
+    """Image of the default plan, which must use `axes`, and of the plain launch."""
+    out = []
+    for allowed in (3, 0):
+        plan = bfm.Plan(desc, None, e_type=e_type)
+        used = _lib.lib().bf_test_set_mirrors(plan._h, allowed)
+        assert used == (axes & allowed)
+        out.append(plan.das(e).cpu().numpy())
+    return out
+
+
+@pytest.mark.parametrize("dims, axes, kw", [
+    ((50, 64, 5), 3, {}),                            # both axes, even
+    ((49, 63, 4), 3, {}),                            # odd: the middle lines are their own images
+    ((64, 49, 4), 3, dict(focal_depth=-8 * MM)),     # diverging
+    ((33, 16, 5), 2, {}),                            # one box along y: x alone
+    ((16, 49, 3), 1, dict(f_number=0.0)),            # y alone, no apodization
+    ((64, 64, 3), 3, dict(interp="linear")),
+    ((64, 64, 3), 0, dict(interp="nearest")),
+])
+def test_mirrored_volume_matches_oracle(torch_mod, dims, axes, kw):
+    desc = _desc(dims, **kw)
+    e = _data(desc)
+    got, plain = _both(torch_mod, desc, torch_mod.from_numpy(e).cuda(), axes)
+    if desc["interp"] == "nearest":
+        assert np.array_equal(got, plain)
+        return
+    ref = oracle.das(desc, e)
+    assert rel_l2(got, ref) <= TOL_L2
+    assert rel_l2(plain, ref) <= TOL_L2
+
+
+@pytest.mark.parametrize("e_type", ["bf16", "i32"])
+def test_mirrored_data_types(torch_mod, e_type):
+    torch = torch_mod
+    desc = _desc((64, 49, 4))
+    e = np.rint(_data(desc) * 1000).astype(np.float32)
+    t = torch.from_numpy(e).cuda().to(torch.bfloat16 if e_type == "bf16" else torch.int32)
+    got, plain = _both(torch, desc, t, 3, e_type)
+    ref = oracle.das(desc, t.to(torch.float32).cpu().numpy())
+    assert rel_l2(got, ref) <= TOL_L2
+    assert rel_l2(plain, ref) <= TOL_L2
+
+
+@pytest.mark.parametrize("dims, axes", [((64, 63, 3), 3), ((16, 40, 5), 1), ((50, 16, 5), 2)])
+def test_mirrored_iq(torch_mod, dims, axes):
+    desc = _desc(dims, S=400)
+    desc.update(iq=True, fs=10e6, t0=0.5e-6)
+    e = _data(desc, iq=True)
+    got, plain = _both(torch_mod, desc, torch_mod.from_numpy(e).cuda(), axes)
+    ref = oracle.das_iq(desc, e[..., 0] + 1j * e[..., 1])
+    assert rel_l2(got, ref) <= TOL_L2
+    assert rel_l2(plain, ref) <= TOL_L2
+
+
+def _shear(desc, r, c, v):
+    desc["xdc"] = np.array(desc["xdc"], dtype=np.float64)
+    desc["xdc"][r, c] += v
+    return desc
+
+
+@pytest.mark.parametrize("make, axes", [
+    (lambda: _desc((64, 64, 3), tx_elements=np.r_[0:12, 13:25]), 3),     # the middle of 25 left out
+    (lambda: _desc((64, 64, 3), tx_elements=np.r_[0:13, 14:25]), 1),     # lopsided
+    (lambda: _desc((64, 64, 3), channel_map=np.roll(np.arange(24), 1)), 2),
+    (lambda: _desc((64, 64, 3), channel_map=np.arange(24)[::-1], tx_elements=np.arange(24)[::-1]), 3),
+    (lambda: _shear(_desc((64, 64, 3)), 1, 3, 0.02 * MM), 2),      # grid offset in y
+    (lambda: _shear(_desc((64, 64, 3)), 0, 3, 1e-6 * MM), 1),      # a nanometre in x
+    (lambda: _shear(_desc((64, 64, 3)), 0, 2, 0.05), 1),           # depth axis leans in x
+    (lambda: _shear(_desc((64, 64, 3)), 1, 0, 0.05), 0),           # x axis leans in y
+    (lambda: _shear(_desc((64, 64, 3)), 2, 1, 0.05), 2),           # depth changes along y
+])
+def test_only_symmetric_axes_are_mirrored(torch_mod, make, axes):
+    desc = make()
+    if int(np.max(desc["tx_elements"])) >= 24:       # 25 columns: the subset skips one
+        desc["n_elem"] = (25, 24)
+        desc["xdc"] = synth.centered_xdc((25, 24), desc["pitch"])
+    e = _data(desc)
+    got, plain = _both(torch_mod, desc, torch_mod.from_numpy(e).cuda(), axes)
+    ref = oracle.das(desc, e)
+    assert rel_l2(got, ref) <= TOL_L2
+    assert rel_l2(plain, ref) <= TOL_L2
+
+
+def test_batched_mirrored_frames(torch_mod):
+    torch = torch_mod
+    n = 24
+    descs = [_desc((64, 64, 4)), _desc((64, 40, 4), channel_map=np.roll(np.arange(n), 1)),
+             _desc((20, 41, 6))]
+    plan = bfm.BatchPlan(descs, [None] * 3)
+    rng = np.random.default_rng(3)
+    rfs = [torch.from_numpy(rng.integers(-3000, 3000, (n, n, 700)).astype(np.int16)).cuda()
+           for _ in descs]
+    outs = [torch.empty(s, device="cuda") for s in plan.out_shapes]
+    refs = [oracle.das(d, r.cpu().numpy().astype(np.float64)) for d, r in zip(descs, rfs)]
+    for step in (plan.run, plan.graph_launch, plan.graph_launch):
+        for o in outs:
+            o.zero_()
+        step(rfs, outs)
+        for o, ref in zip(outs, refs):
+            assert rel_l2(o.cpu().numpy(), ref) <= TOL_L2

@@ -23,11 +23,13 @@
 // sliding 8-word register window refilled by one aligned 16-byte LDS read per
 // 4 taps, so every LDS word read feeds 4 outputs (the paper's LDS sharing,
 // carried one level further into registers).  Taps are workgroup-uniform and
-// come through scalar loads.
+// come through scalar loads.  Longer filters and larger decimations run the
+// same chains of FMAs on the FP32 matrix cores (demod_mfma_kernel).
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "bf.h"
@@ -108,6 +110,57 @@ __device__ inline void fir_phase(const float4 *wp, const float2 *__restrict__ gp
             }
         }
         lo = hi;
+    }
+}
+
+// Rotates and stores the 4 consecutive outputs q .. q + 3 of a trace from the
+// real and imaginary filter sums of its mixed taps.
+template <int OT>
+__device__ inline void store_outputs(const DemodArgs &a, int trace, int q, const float (&ar)[DEMOD_M],
+                                     const float (&ai)[DEMOD_M])
+{
+    if (q >= a.n_out) return;
+    const long o = (long)trace * a.n_out + q;
+    if (q + DEMOD_M <= a.n_out) {
+        const float4 r01 = *reinterpret_cast<const float4 *>(a.rot + q);
+        const float4 r23 = *reinterpret_cast<const float4 *>(a.rot + q + 2);
+        const float rx[4] = {r01.x, r01.z, r23.x, r23.z}, ry[4] = {r01.y, r01.w, r23.y, r23.w};
+        float yr[4], yi[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            yr[m] = fmaf(ar[m], rx[m], -ai[m] * ry[m]);
+            yi[m] = fmaf(ar[m], ry[m], ai[m] * rx[m]);
+        }
+        if constexpr (OT == BF_IQ_I16) {
+            uint4 v;
+            v.x = sat_pk_i16(yr[0], yi[0]);
+            v.y = sat_pk_i16(yr[1], yi[1]);
+            v.z = sat_pk_i16(yr[2], yi[2]);
+            v.w = sat_pk_i16(yr[3], yi[3]);
+            uint32_t *dst = static_cast<uint32_t *>(a.y) + o;
+            if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+                *reinterpret_cast<uint4 *>(dst) = v;
+            } else {
+                dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+            }
+        } else {
+            float2 *dst = static_cast<float2 *>(a.y) + o;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) dst[m] = make_float2(yr[m], yi[m]);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < DEMOD_M; ++m) {
+            if (q + m >= a.n_out) break;
+            const float2 r = a.rot[q + m];
+            const float yr = fmaf(ar[m], r.x, -ai[m] * r.y);
+            const float yi = fmaf(ar[m], r.y, ai[m] * r.x);
+            if constexpr (OT == BF_IQ_I16)
+                static_cast<uint32_t *>(a.y)[o + m] =
+                    (uint16_t)sat_i16(yr) | ((uint32_t)(uint16_t)sat_i16(yi) << 16);
+            else
+                static_cast<float2 *>(a.y)[o + m] = make_float2(yr, yi);
+        }
     }
 }
 
@@ -197,49 +250,141 @@ __global__ __launch_bounds__(T) void demod_kernel(DemodArgs a)
         }
         gp += nb4;
     }
-    const int q = q0 + t * DEMOD_M;
-    if (q >= a.n_out) return;
-    const long o = (long)trace * a.n_out + q;
-    if (q + DEMOD_M <= a.n_out) {
-        const float4 r01 = *reinterpret_cast<const float4 *>(a.rot + q);
-        const float4 r23 = *reinterpret_cast<const float4 *>(a.rot + q + 2);
-        const float rx[4] = {r01.x, r01.z, r23.x, r23.z}, ry[4] = {r01.y, r01.w, r23.y, r23.w};
-        float yr[4], yi[4];
+    store_outputs<OT>(a, trace, q0 + t * DEMOD_M, ar, ai);
+}
+
+// ---------------------------------------------------------------------------
+// The same filter on the FP32 matrix cores (longer filters).
+//
+// One polyphase component of 16 consecutive outputs of 16 traces is a product
+// of a banded Toeplitz matrix of its taps (row o, column k: tap k - o) with the
+// component's words of the 16 traces: v_mfma_f32_16x16x4_f32, A = taps, B =
+// samples, one product for the real and one for the imaginary parts of the
+// taps.  The band fills nb / (nb + 15) of the columns (nb taps a component),
+// and the matrix cores run FP32 at twice the rate of the vector units.  The
+// instruction adds its four products one after the other, each a fused
+// multiply-add, in the order of k, and a zero outside the band leaves the sum
+// as it is: every output is the same chain of FMAs as demod_kernel's, bit for
+// bit (the tests compare the two).
+//
+// A workgroup stages the int16 samples of 16 traces (converted on the way
+// from LDS to the operand) and the padded taps once; each of its 4
+// wavefronts computes T tiles of 16 outputs, whose products share the tap
+// operand.  Rows of 16 traces lie 4 banks apart, so the 64 lanes of a sample
+// read (16 traces x 4 words) fall in different banks for D <= 2.
+// 16 384 traces x 2816 samples, 166 complex taps, D = 2: 336 us on the vector
+// units (46 TFLOP/s), 180 us here (86; the Toeplitz products run at 101,
+// 83 / 98 of them on taps).
+// ---------------------------------------------------------------------------
+constexpr int DEMOD_TR = 16;          // traces per workgroup
+
+struct DemodTile {
+    int groups;           // groups of 16 traces
+    int stride;           // int16 samples per staged trace row (multiple of 8)
+    int rows8;            // 16-byte chunks staged per row
+    float inv_rows8;      // 1 / rows8
+};
+
+typedef float demod_v4f __attribute__((ext_vector_type(4)));
+
+// Columns (words) of a component's Toeplitz product, a multiple of 4, and the
+// entries of its padded tap table (tap k at entry k + 15).
+__host__ __device__ inline int toeplitz_cols(int nb) { return nb > 0 ? (nb + 15 + 3) & ~3 : 0; }
+__host__ __device__ inline int toeplitz_taps(int nb) { return nb > 0 ? toeplitz_cols(nb) + 16 : 0; }
+
+template <int OT, int T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+void demod_mfma_kernel(DemodArgs a, DemodTile m)
+{
+    extern __shared__ float4 xs4[];
+    int16_t *xs = reinterpret_cast<int16_t *>(xs4);                       // [16][stride]
+    float2 *tap = reinterpret_cast<float2 *>(xs + DEMOD_TR * m.stride);   // padded taps
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int grp = blockIdx.x / a.chunks;
+    const int q0 = (blockIdx.x - grp * a.chunks) * (64 * T);
+    const int n0 = q0 * a.D - (a.n_taps - 1);       // word w of component ph: n0 + ph + D w
+    const int n_al = n0 & ~7;
+    // the 16 rows' chunks are dealt to the threads in order, four loads in
+    // flight per thread (chunk e: (e + 1/2) / rows8 is at least 1 / (2 rows8)
+    // away from an integer, far more than the FP32 rounding of the product)
+    const int total = DEMOD_TR * m.rows8;
+    for (int e0 = threadIdx.x; e0 < total; e0 += 4 * 256) {
+        int4 v[4];
+        int dst[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            yr[m] = fmaf(ar[m], rx[m], -ai[m] * ry[m]);
-            yi[m] = fmaf(ar[m], ry[m], ai[m] * rx[m]);
-        }
-        if constexpr (OT == BF_IQ_I16) {
-            uint4 v;
-            v.x = sat_pk_i16(yr[0], yi[0]);
-            v.y = sat_pk_i16(yr[1], yi[1]);
-            v.z = sat_pk_i16(yr[2], yi[2]);
-            v.w = sat_pk_i16(yr[3], yi[3]);
-            uint32_t *dst = static_cast<uint32_t *>(a.y) + o;
-            if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-                *reinterpret_cast<uint4 *>(dst) = v;
+        for (int u = 0; u < 4; ++u) {
+            const int e = min(e0 + 256 * u, total - 1);
+            const int r = (int)(((float)e + 0.5f) * m.inv_rows8), c = e - r * m.rows8;
+            const int n = n_al + 8 * c;
+            const int16_t *x = a.x + (long)min(grp * DEMOD_TR + r, a.n_traces - 1) * a.S;
+            dst[u] = r * m.stride + 8 * c;
+            if (n >= 0 && n + 8 <= a.S) {
+                __builtin_memcpy(&v[u], x + n, 16);    // (2-byte aligned rows are allowed)
             } else {
-                dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+                uint32_t w[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int lo = n + 2 * i, hi = lo + 1;
+                    w[i] = (lo >= 0 && lo < a.S ? (uint16_t)x[lo] : 0u) |
+                           ((hi >= 0 && hi < a.S ? (uint32_t)(uint16_t)x[hi] : 0u) << 16);
+                }
+                v[u] = make_int4(w[0], w[1], w[2], w[3]);
             }
-        } else {
-            float2 *dst = static_cast<float2 *>(a.y) + o;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) dst[m] = make_float2(yr[m], yi[m]);
         }
-    } else {
 #pragma unroll
-        for (int m = 0; m < DEMOD_M; ++m) {
-            if (q + m >= a.n_out) break;
-            const float2 r = a.rot[q + m];
-            const float yr = fmaf(ar[m], r.x, -ai[m] * r.y);
-            const float yi = fmaf(ar[m], r.y, ai[m] * r.x);
-            if constexpr (OT == BF_IQ_I16)
-                static_cast<uint32_t *>(a.y)[o + m] =
-                    (uint16_t)sat_i16(yr) | ((uint32_t)(uint16_t)sat_i16(yi) << 16);
-            else
-                static_cast<float2 *>(a.y)[o + m] = make_float2(yr, yi);
+        for (int u = 0; u < 4; ++u) *reinterpret_cast<int4 *>(xs + dst[u]) = v[u];
+    }
+    {
+        const float2 *g = a.g;
+        float2 *dst = tap;
+        for (int ph = 0; ph < a.D; ++ph) {
+            const int nb = phase_taps(a.n_taps, a.D, ph), nt = toeplitz_taps(nb);
+            for (int e = threadIdx.x; e < nt; e += 256)
+                dst[e] = e >= 15 && e - 15 < nb ? g[e - 15] : make_float2(0.f, 0.f);
+            g += phase_taps4(a.n_taps, a.D, ph);
+            dst += nt;
         }
+    }
+    __syncthreads();
+    const int col = lane & 15, kq = lane >> 4;
+    demod_v4f cr[T], ci[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) cr[t] = ci[t] = {0.f, 0.f, 0.f, 0.f};
+    const int16_t *xrow = xs + col * m.stride + (n0 - n_al) + a.D * (16 * T * wave + kq);
+    const float2 *tp = tap + (15 + kq - col);       // entry of tap k - o for row o = col, k = kq
+    auto product = [&](int ph, int steps, auto kind) {
+        constexpr int KIND = decltype(kind)::value;
+        const int16_t *xp = xrow + ph;
+#pragma unroll 2
+        for (int s = 0; s < steps; ++s) {
+            const float2 g = tp[4 * s];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const float f = (float)xp[a.D * (4 * s + 16 * t)];
+                if constexpr (KIND != TAPS_IMAG)
+                    cr[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.x, f, cr[t], 0, 0, 0);
+                if constexpr (KIND != TAPS_REAL)
+                    ci[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.y, f, ci[t], 0, 0, 0);
+            }
+        }
+    };
+    for (int ph = 0; ph < a.D; ++ph) {
+        const int nb = phase_taps(a.n_taps, a.D, ph), steps = toeplitz_cols(nb) >> 2;
+        switch (a.kind[ph]) {
+            case TAPS_REAL: product(ph, steps, std::integral_constant<int, TAPS_REAL>()); break;
+            case TAPS_IMAG: product(ph, steps, std::integral_constant<int, TAPS_IMAG>()); break;
+            default: product(ph, steps, std::integral_constant<int, TAPS_COMPLEX>()); break;
+        }
+        tp += toeplitz_taps(nb);
+    }
+    // accumulator layout: lane (col, kq) holds outputs 4 kq .. 4 kq + 3 of trace col
+    const int trace = grp * DEMOD_TR + col;
+    if (trace >= a.n_traces) return;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const float yr4[4] = {cr[t][0], cr[t][1], cr[t][2], cr[t][3]};
+        const float yi4[4] = {ci[t][0], ci[t][1], ci[t][2], ci[t][3]};
+        store_outputs<OT>(a, trace, q0 + 16 * (T * wave + t) + 4 * kq, yr4, yi4);
     }
 }
 
@@ -297,6 +442,57 @@ static void cis_rev(double f, double *c, double *s)
     }
     *c = cos(2.0 * M_PI * f);
     *s = sin(2.0 * M_PI * f);
+}
+
+template <int T>
+static void launch_mfma_t(const DemodArgs &a, const DemodTile &m, int out_type, size_t shm, hipStream_t s)
+{
+    const dim3 grid((unsigned)(m.groups * a.chunks));
+    if (out_type == BF_IQ_I16)
+        hipLaunchKernelGGL((demod_mfma_kernel<BF_IQ_I16, T>), grid, dim3(256), shm, s, a, m);
+    else
+        hipLaunchKernelGGL((demod_mfma_kernel<BF_IQ_F32, T>), grid, dim3(256), shm, s, a, m);
+}
+
+// Launches the matrix-core kernel where it is the faster one: for filters of
+// 61 taps and more, for decimations from 3 (whose staging splits into words
+// of components on the vector units), and from 2^23 outputs on from 32 / D
+// taps.  Vector units against matrix cores, us, D = 1 / 2 / 4: 16 384 x 2816
+// samples, 16 taps 106 129 / 82 76 / 58 57, 36 taps 142 131 / 103 77 / 75 61,
+// 166 taps 482 317 / 305 119 / 165 96; 4096 x 2047 samples, 36 taps 29 33 / 18
+// 21 / 24 17, 100 taps 56 49 / 29 25 / 33 21.
+// T = 2 tiles per wavefront (4 measured 10 % slower, its accumulators halve
+// the occupancy; 1 up to 20 %), 1 where that leaves fewer than 1024 workgroups
+// or two tiles' samples exceed 64 KiB.
+static bool launch_demod_mfma(bf_demod d, DemodArgs a, hipStream_t s)
+{
+    const bool large = (long)a.n_traces * a.n_out >= (1L << 23) && a.n_taps * a.D >= 32;
+    if (a.n_taps < 61 && a.D < 3 && !large) return false;
+    DemodTile m;
+    m.groups = (a.n_traces + DEMOD_TR - 1) / DEMOD_TR;
+    int nbmax = 0, tap_words = 0;
+    for (int ph = 0; ph < a.D; ++ph) {
+        const int nb = phase_taps(a.n_taps, a.D, ph);
+        tap_words += toeplitz_taps(nb);
+        nbmax = std::max(nbmax, nb);
+    }
+    for (int T = 2; T >= 1; --T) {
+        const int words = 64 * T - 16 + toeplitz_cols(nbmax);
+        m.rows8 = (a.D * words + 7 + 7) / 8;
+        m.inv_rows8 = 1.f / (float)m.rows8;
+        m.stride = ((8 * m.rows8 + 127) & ~127) + 8;
+        const size_t shm = (size_t)DEMOD_TR * m.stride * 2 + (size_t)tap_words * 8;
+        a.chunks = (a.n_out + 64 * T - 1) / (64 * T);
+        const long blocks = (long)m.groups * a.chunks;
+        if (T == 2 && (shm > 64 * 1024 || blocks < 1024)) continue;
+        if (shm > 64 * 1024 || blocks >= (1L << 31)) return false;
+        if (T == 2)
+            launch_mfma_t<2>(a, m, d->p.out_type, shm, s);
+        else
+            launch_mfma_t<1>(a, m, d->p.out_type, shm, s);
+        return true;
+    }
+    return false;
 }
 
 extern "C" {
@@ -402,13 +598,19 @@ int bf_demodulate(bf_demod d, const int16_t *rf, void *iq, void *stream)
     a.n_out = d->n_out;
     a.D = d->p.decimation;
     a.n_taps = d->p.n_taps;
+    for (int ph = 0; ph < 16; ++ph) a.kind[ph] = d->kind[ph];
+    a.chunks = a.phase_len = 0;
+    a.lg_d = -1;
+    if (launch_demod_mfma(d, a, (hipStream_t)stream)) {
+        hipError_t e = hipGetLastError();
+        return e == hipSuccess ? BF_OK : hip_fail(e, "demodulation launch");
+    }
     // Workgroup of T threads x 4 outputs; each component needs the words of
     // T*4 outputs plus its padded taps plus the window's 4-word prefetch.
     int nb4max = 0;
     for (int ph = 0; ph < a.D; ++ph) nb4max = std::max(nb4max, phase_taps4(a.n_taps, a.D, ph));
     const int T = (a.D * (256 * DEMOD_M + nb4max + 4) * 4 <= 48 * 1024) ? 256 : 64;
     a.chunks = (d->n_out + T * DEMOD_M - 1) / (T * DEMOD_M);
-    for (int ph = 0; ph < 16; ++ph) a.kind[ph] = d->kind[ph];
     a.phase_len = T * DEMOD_M + nb4max + 4;
     // vector staging: D a power of two, every trace row 16-byte aligned
     a.lg_d = -1;

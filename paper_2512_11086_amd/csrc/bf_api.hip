@@ -676,12 +676,20 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
 // (measured best against 4 to 64 on the 256 x 256 FORCES plane and the
 // 128 x 128 x 256 HERCULES volume), fewer for shallow grids; the rest of the
 // lanes and the workgroup's 8 wavefronts lie side by side laterally.
+// Coarser depth steps lengthen the windows, and with them the flushes, by the
+// same factor, while fewer lanes along depth already reach separate entries:
+// a HERCULES volume takes 8 from 5.7 samples per step on and 4 from 9 (us with
+// 16, 8, 4 lanes: 3.8 samples 94 400 116 000 174 000; 5.1 361 429 665; 5.8
+// 2 960 2 420 3 640; 6.2 710 556 599; 9.3 230 139 190; 13.1 1 880 977 814; 15.7
+// 2 460 1 420 1 230).
 void Frame::adjoint_e_tile(DasArgs *a, int bw_out[3]) const
 {
     const int zp = variant == BF_DAS_LDS_Z2 && z2_ok() ? 2 : 1;
     const int nzl = (grid.nz + zp - 1) / zp;
+    const double step = 2.0 * a->k * fabs(grid.az[2]);     // samples per depth point
+    const int lz_max = p.mode != BF_HERCULES_3D || step < 5.7 ? 4 : step < 9.0 ? 3 : 2;
     int lz = 0;
-    while (lz < 4 && (1 << lz) < nzl) ++lz;
+    while (lz < lz_max && (1 << lz) < nzl) ++lz;
     const int r = 6 - lz;
     if (grid.ny == 1) {
         a->lx = r;
@@ -691,6 +699,7 @@ void Frame::adjoint_e_tile(DasArgs *a, int bw_out[3]) const
         a->lx = (r + 1) / 2;
         a->ly = r / 2;
         bw_out[0] = 4; bw_out[1] = 2; bw_out[2] = 1;
+        if (lz == 3 && lz_max == 3) { bw_out[0] = 2; bw_out[1] = 4; }     // (square box, 4 x 2 x 8 lanes)
     }
     a->lz = lz;
     a->tiles_x = (grid.nx + (1 << a->lx) - 1) >> a->lx;

@@ -6,17 +6,22 @@
 // column is |x_a| with x_a its analytic signal along depth:
 //     X = DFT_N(x),  X_a[k] = h[k] X[k]  (h = 1 at DC and Nyquist, 2 for
 //     positive, 0 for negative frequencies),  x_a = IDFT_N(X_a).
-// Power-of-two N from 64 to 1024: one wavefront per two columns (packed as
-// one complex sequence, see env_fft_reg_kernel), FFT held in registers (four-step split N = 64 M: a 64-point FFT across the lanes by
+// Power-of-two N from 64 to 256: env_fft_tile_kernel, two columns packed as one
+// complex sequence, N = R L with R values in each of L lanes, FFTs inside the
+// lanes and one transposition through LDS each way.  N = 512 and 1024: one
+// wavefront per two columns (packed alike, env_fft_reg_kernel), FFT held in
+// registers (four-step split N = 64 M: a 64-point FFT across the lanes by
 // xor-partner exchanges, a twiddle, an M-point FFT inside each lane, then the
-// mirror image for the inverse); no LDS passes and no barriers.  Other
-// power-of-two N: one workgroup per column, radix-2 FFT in LDS (forward
-// decimation-in-time from a bit-reversed load, spectrum weighting, inverse
-// decimation-in-frequency, read back in bit-reversed order).  Twiddles come
-// from a host-FP64, stage-major table in global memory (stage len holds
-// exp(-j 2 pi pos / len) for pos < len / 2 at offset len / 2 - 1), so the
-// lanes of a stage read consecutive entries (cached; no LDS bank conflicts).  Other N: Re x_a = x exactly, and Im x_a is the
-// circular convolution of x with q = Im IDFT(h) (host FP64), summed directly.
+// mirror image for the inverse); no LDS passes and no barriers.  Other power-of-two N: one
+// workgroup per column, radix-2 FFT in LDS (forward decimation-in-time from a
+// bit-reversed load, spectrum weighting, inverse decimation-in-frequency, read
+// back in bit-reversed order).  Twiddles come from a host-FP64, stage-major
+// table in global memory (stage len holds exp(-j 2 pi pos / len) for pos <
+// len / 2 at offset len / 2 - 1), so the lanes of a stage read consecutive
+// entries (cached; no LDS bank conflicts).  Other N: Re x_a = x exactly, and
+// Im x_a is the circular convolution of x with q = Im IDFT(h) (host FP64): a
+// circulant product on the matrix cores (env_circ_kernel), or summed directly
+// below 24 and above 1000 samples.
 // IQ images already are analytic: the envelope is |z|.
 //
 // Compression (ref > 0 is fused into the store; ref <= 0 uses the image
@@ -44,11 +49,14 @@ struct EnvArgs {
     float *out;              // [n_cols][N]
     const float2 *tw;        // FFT: [N - 1] stage-major twiddles (see above)
     const float2 *tw_lane;   // register FFT: [6][64] W_{2d}^{l mod d}, d = 32, 16, .., 1
-    const float2 *tw_mid;    // register FFT: [64][M] W_N^{r bitrev6(l)}
+    const float2 *tw_mid;    // register FFT: [64][M] W_N^{r bitrev6(l)}; tile FFT: [R][L] W_N^{k l}
     float2 wm[8];            // register FFT: W_M^j, j < M / 2
     const float *q;          // direct path: [N] Im IDFT(h)
     float *part_max;         // [n_parts] per-workgroup maxima (ref <= 0)
     float *img_max;          // reduced maximum (ref <= 0)
+    int n_parts;             // partial maxima the compression pass reduces itself (0: img_max)
+    int given;               // ref is the maximum of part_max (second pass of the tile FFT)
+    int vec;                 // out holds whole 16-byte groups (compression pass)
     long n_cols;
     int N, log2n;
     int compress;
@@ -93,8 +101,32 @@ __device__ inline void publish_max(const EnvArgs &a, float local_max)
     if (threadIdx.x == 0) {
         float m = s_max[0];
         for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmaxf(m, s_max[w]);
-        a.part_max[blockIdx.x] = m;
+        a.part_max[blockIdx.x + gridDim.x * blockIdx.y] = m;
     }
+}
+
+// The image maximum from the partial maxima, by every workgroup for itself (at
+// most ENV_FEW_PARTS of them).
+constexpr int ENV_FEW_PARTS = 2048;
+__device__ inline float max_of_parts(const EnvArgs &a)
+{
+    __shared__ float s[4];
+    float m = 0.f;
+    for (int i = threadIdx.x; i < a.n_parts; i += blockDim.x) m = fmaxf(m, a.part_max[i]);
+    for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = s[0];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmaxf(m, s[w]);
+    return m;
+}
+
+// One value compressed by the image maximum a.ref (an all-zero image gives
+// -param or 0).
+__device__ inline float compress_by_max(const EnvArgs &a, float env)
+{
+    return a.ref > 0.f ? compress_value(env, a.compress, a.inv_ref, a.param)
+                       : a.compress == BF_COMPRESS_LOG ? -a.param : 0.f;
 }
 
 __device__ inline float2 cmul(float2 a, float2 b)
@@ -186,7 +218,116 @@ __global__ __launch_bounds__(256) void env_direct_kernel(EnvArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Register FFT (64 <= N = 64 M <= 1024): sample n = M l + r lives in lane l,
+// Any N up to ENV_CIRC_MAX on the FP32 matrix cores: y = Im x_a of 16 columns
+// is a circulant matrix of q times the columns (v_mfma_f32_16x16x4_f32, tiles of
+// 16 outputs x 16 columns).  For even N, q is 0 at even distances, so even
+// outputs read odd samples only and odd outputs even ones: two products of
+// half the size (P = 2 phases of H = N / P outputs).
+//
+// The direct sum reads two LDS words per FMA and thread and wastes the lanes
+// past N; here one word of q and one of x feed 16 FMAs.  us, direct and here:
+// 96 x 96 columns of 192 43.7, 13.6; 60 x 70 of 251 34.2, 20.0; 128 x 128 of 300
+// 181, 45.
+//
+// Few columns (less than a workgroup per CU) spread their tiles over several
+// workgroups, which then store their outputs from the accumulators.
+//
+// LDS: the columns by phase ([16][stride], phase pe at pe H4; stride = 4 modulo
+// 64 words, so 16 columns x 4 samples fall in different banks), their
+// envelopes (same shape), and q by distance: entry d + H4 + 3 holds the q of
+// outputs o and samples m of a phase with d = o - m (+ the phase's shift).
+// ---------------------------------------------------------------------------
+constexpr int ENV_CIRC_MIN = 24, ENV_CIRC_MAX = 1000;
+typedef float env_v4f __attribute__((ext_vector_type(4)));
+
+struct EnvCirc {
+    int P, H, H4;         // phases, outputs (= samples) per phase, rounded up to 4
+    int tiles;            // 16-output tiles per phase
+    int stride;           // words per column
+    int nq;               // entries of the q table
+};
+static EnvCirc env_circ(int n)
+{
+    EnvCirc c;
+    c.P = n % 2 == 0 ? 2 : 1;
+    c.H = n / c.P;
+    c.H4 = (c.H + 3) & ~3;
+    c.tiles = (c.H + 15) / 16;
+    c.stride = ((c.P * c.H4 + 63) & ~63) + 4;
+    c.nq = c.H4 + 16 * c.tiles + 4;
+    return c;
+}
+static size_t env_circ_lds(const EnvCirc &c) { return ((size_t)2 * 16 * c.stride + c.nq) * sizeof(float); }
+
+__global__ __launch_bounds__(256) void env_circ_kernel(EnvArgs a, EnvCirc c)
+{
+    extern __shared__ float sf[];
+    float *xs = sf, *env = sf + 16 * c.stride, *qs = env + 16 * c.stride;
+    const int N = a.N, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long col0 = (long)blockIdx.x * 16;
+    const int cols = (int)min(16L, a.n_cols - col0);
+    for (int i = threadIdx.x; i < 16 * c.stride; i += 256) xs[i] = 0.f;
+    // distance d = i - (H4 + 3) between output o and sample m of a phase's
+    // product: q index 2 d + 1 (even N: odd output 2 o + 1, even sample 2 m;
+    // the even outputs 2 o and odd samples 2 m + 1 are one step nearer) or d
+    for (int i = threadIdx.x; i < c.nq; i += 256) {
+        int k = c.P == 2 ? 2 * (i - c.H4 - 3) + 1 : i - c.H4 - 3;
+        k %= N;
+        qs[i] = a.q[k < 0 ? k + N : k];
+    }
+    __syncthreads();
+    const float *img = a.img + col0 * N;
+    for (int g = wave; g < cols; g += 4)
+        for (int n = lane; n < N; n += 64)
+            xs[g * c.stride + (c.P == 2 ? (n & 1) * c.H4 + (n >> 1) : n)] = img[(long)g * N + n];
+    __syncthreads();
+    const int col = lane & 15, kq = lane >> 4;
+    const int total = c.P * c.tiles;
+    float local_max = 0.f;
+    for (int t = blockIdx.y * 4 + wave; t < total; t += 4 * gridDim.y) {
+        const int ph = t / c.tiles;                         // parity of the outputs (P = 2)
+        const int o0 = 16 * (t - ph * c.tiles);
+        // row i = col of the operand: q at o0 + i - m, m = 4 s + kq
+        const int shift = c.P == 2 && ph == 0 ? 1 : 0;
+        const float *qp = qs + (c.H4 + 3) + o0 + col - kq - shift;
+        const float *xp = xs + col * c.stride + (c.P == 2 ? (1 - ph) * c.H4 : 0) + kq;
+        // four accumulators: independent products, and chains a quarter as
+        // long (relative error 6.5e-8 at N = 192, 1.0e-7 of the direct sum)
+        env_v4f acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        int m = 0;
+        for (; m + 16 <= c.H4; m += 16) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(qp[-m - 4 * u], xp[m + 4 * u], acc[u], 0, 0, 0);
+        }
+        for (; m < c.H4; m += 4)
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(qp[-m], xp[m], acc[0], 0, 0, 0);
+        // accumulator: outputs o0 + 4 kq + r of column col
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int o = o0 + 4 * kq + r;
+            if (o >= c.H) continue;
+            const int w = col * c.stride + ph * (c.P == 2 ? c.H4 : 0) + o;
+            const float x = xs[w], y = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+            const float e = sqrtf(fmaf(x, x, y * y));
+            if (gridDim.y == 1)
+                env[w] = e;
+            else if (col < cols)
+                store_env(a, (col0 + col) * N + c.P * o + (c.P == 2 ? ph : 0), e, local_max);
+        }
+    }
+    if (gridDim.y == 1) {        // whole columns: contiguous stores
+        __syncthreads();
+        for (int g = wave; g < cols; g += 4)
+            for (int n = lane; n < N; n += 64)
+                store_env(a, (col0 + g) * N + n,
+                          env[g * c.stride + (c.P == 2 ? (n & 1) * c.H4 + (n >> 1) : n)], local_max);
+    }
+    publish_max(a, local_max);
+}
+
+// ---------------------------------------------------------------------------
+// Register FFT (N = 64 M = 512 or 1024): sample n = M l + r lives in lane l,
 // register r.  X[k1 + 64 k2] = sum_r W_M^{r k2} W_N^{r k1} [sum_l x[M l + r] W_64^{l k1}].
 // ---------------------------------------------------------------------------
 // Value of lane l ^ m (m a power of two, constant after unrolling).  Lane
@@ -349,6 +490,191 @@ __global__ __launch_bounds__(256) void env_fft_reg_kernel(EnvArgs a)
     publish_max(a, local_max);
 }
 
+// ---------------------------------------------------------------------------
+// Tile FFT (64 <= N <= 256, N = R L, R >= L): sample n = n1 L + n2 lives in
+// register n1 of lane n2; L lanes hold one pair of columns, so a wavefront
+// holds 64 / L pairs.
+//   X[k1 + R k2] = sum_n2 W_L^{n2 k2} [ W_N^{n2 k1} sum_n1 W_R^{n1 k1} x[n1 L + n2] ]
+// The inner sum is an R-point FFT inside the lane; after a transposition
+// through LDS a lane holds the R / L bins k1 = u L + lane with all their n2,
+// and the outer sum is R / L FFTs of L points inside the lane.  The inverse
+// retraces the steps.
+//
+// The 128 x 128 x 256 volume: 17.8 us with a 64-point FFT across the lanes
+// (exchanges of every value in each of its 12 stages, about 700 vector
+// instructions per pair of columns, VALU-bound), 9.6 us here with about 240 per
+// pair (reading and writing the volume takes 6.6 us).  N = 512 and 1024 stay
+// with the FFT across the lanes: 32 values per lane unroll to code that a
+// wavefront runs once, bound by its instruction fetch (1 x 400 columns of 512
+// 15.8 us against 8.4, 64 x 64 17.5 against 13.7).
+// ---------------------------------------------------------------------------
+// cos(pi k / 16)
+__device__ constexpr float COS16[17] = {1.0000000000f, 0.9807852804f, 0.9238795325f, 0.8314696123f, 0.7071067812f, 0.5555702330f, 0.3826834324f, 0.1950903220f, 0.0000000000f, -0.1950903220f, -0.3826834324f, -0.5555702330f, -0.7071067812f, -0.8314696123f, -0.9238795325f, -0.9807852804f, -1.0000000000f};
+
+// v times exp(-+ j 2 pi J / M) (M a power of two up to 32, J < M / 2): forward
+// - (INV = false), inverse +.  Quarter and eighth turns without a full product.
+template <int M, int J, bool INV>
+__device__ inline float2 turn(float2 v)
+{
+    if constexpr (J == 0) {
+        return v;
+    } else if constexpr (4 * J == M) {
+        return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
+    } else {
+        constexpr int K = 32 / M * J;                       // 16ths of a half turn
+        constexpr float c = COS16[K];
+        constexpr float s0 = K <= 8 ? COS16[8 - K] : COS16[K - 8];    // sin(pi K / 16)
+        constexpr float s = INV ? s0 : -s0;
+        if constexpr (8 * J == M || 8 * J == 3 * M) {       // |c| = |s|
+            constexpr float h = 0.70710678118654752f;
+            const float sum = v.x + v.y, dif = v.x - v.y;
+            if constexpr (8 * J == M) return INV ? make_float2(h * dif, h * sum) : make_float2(h * sum, -h * dif);
+            return INV ? make_float2(-h * sum, h * dif) : make_float2(-h * dif, -h * sum);
+        }
+        return make_float2(fmaf(v.x, c, -v.y * s), fmaf(v.x, s, v.y * c));
+    }
+}
+
+__host__ __device__ constexpr int log2_of(int m) { return m <= 1 ? 0 : 1 + log2_of(m / 2); }
+__host__ __device__ constexpr int bit_reverse(int v, int bits)
+{
+    return bits == 0 ? 0 : ((v & 1) << (bits - 1)) | bit_reverse(v >> 1, bits - 1);
+}
+
+// M-point DFT of v[0 .. M): decimation in frequency, natural order in, bin
+// bit_reverse(p) in register p out.
+template <int M, int J = 0>
+__device__ inline void fft_dif(float2 *v)
+{
+    if constexpr (M > 1) {
+        if constexpr (J < M / 2) {
+            const float2 a = v[J], b = v[J + M / 2];
+            v[J] = make_float2(a.x + b.x, a.y + b.y);
+            v[J + M / 2] = turn<M, J, false>(make_float2(a.x - b.x, a.y - b.y));
+            fft_dif<M, J + 1>(v);
+        } else {
+            fft_dif<M / 2>(v);
+            fft_dif<M / 2>(v + M / 2);
+        }
+    }
+}
+// The inverse (unscaled): bit-reversed bins in, natural order out.
+template <int M, int J>
+__device__ inline void fft_dit_stage(float2 *v)
+{
+    if constexpr (J < M / 2) {
+        const float2 a = v[J], b = turn<M, J, true>(v[J + M / 2]);
+        v[J] = make_float2(a.x + b.x, a.y + b.y);
+        v[J + M / 2] = make_float2(a.x - b.x, a.y - b.y);
+        fft_dit_stage<M, J + 1>(v);
+    }
+}
+template <int M>
+__device__ inline void fft_dit(float2 *v)
+{
+    if constexpr (M > 1) {
+        fft_dit<M / 2>(v);
+        fft_dit<M / 2>(v + M / 2);
+        fft_dit_stage<M, 0>(v);
+    }
+}
+
+// Pairs of columns of a wavefront, LDS float2 of a wavefront.
+template <int R, int L> struct EnvTile {
+    static constexpr int pairs = 64 / L;
+    static constexpr int lds = pairs * R * (L + 1);
+};
+
+// Two real columns per lane group.  The Hilbert transform H is linear with a
+// real kernel, so for z = x1 + j x2 the inverse DFT of -j sgn(k) DFT(z) (sgn =
+// 0 at DC and Nyquist, +1 for positive and -1 for negative frequencies) is
+// H{x1} + j H{x2}, and each envelope is |x_a| = sqrt(x^2 + H{x}^2): the
+// analytic signal of both columns for one complex FFT pair.  A wavefront uses
+// its own part of LDS only: no barriers.
+// MAX: the maximum alone, nothing is stored.  a.given: ref is the maximum that
+// pass left in part_max.
+template <int R, int L, bool MAX>
+__global__ __launch_bounds__(256) void env_fft_tile_kernel(EnvArgs a)
+{
+    extern __shared__ float2 sm[];
+    constexpr int N = R * L, U = R / L, B = log2_of(R), BL = log2_of(L);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l = lane % L, g = lane / L;
+    float2 *buf = sm + wave * EnvTile<R, L>::lds + g * R * (L + 1);
+    const long col =
+        (((long)blockIdx.x * (blockDim.x >> 6) + wave) * EnvTile<R, L>::pairs + g) * 2;
+    const bool has1 = col < a.n_cols, has2 = col + 1 < a.n_cols;
+    const float *x = a.img + col * N + l;
+    const float2 *tw = a.tw_mid + l;
+    float x1[R], x2[R];
+    float2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        x1[r] = has1 ? x[r * L] : 0.f;
+        x2[r] = has2 ? x[N + r * L] : 0.f;
+        v[r] = make_float2(x1[r], x2[r]);
+    }
+    fft_dif<R>(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        constexpr int b = B;
+        const int k1 = bit_reverse(r, b);
+        buf[k1 * (L + 1) + l] = cmul(v[r], tw[k1 * L]);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        float2 w[L];
+        float2 *row = buf + (u * L + l) * (L + 1);
+#pragma unroll
+        for (int n2 = 0; n2 < L; ++n2) w[n2] = row[n2];
+        fft_dif<L>(w);
+        // -j sgn(k) on X[k1 + R k2], k1 = u L + l: k is positive for k2 < L / 2,
+        // negative above, DC and Nyquist at k1 = 0 of k2 = 0 and L / 2
+        const float edge = u == 0 && l == 0 ? 0.f : 1.f;
+#pragma unroll
+        for (int r = 0; r < L; ++r) {
+            const int k2 = bit_reverse(r, BL);
+            float2 z = 2 * k2 < L ? make_float2(w[r].y, -w[r].x) : make_float2(-w[r].y, w[r].x);
+            if (k2 == 0 || 2 * k2 == L) z = make_float2(edge * z.x, edge * z.y);
+            w[r] = z;
+        }
+        fft_dit<L>(w);
+#pragma unroll
+        for (int n2 = 0; n2 < L; ++n2) row[n2] = w[n2];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int k1 = bit_reverse(r, B);
+        const float2 t = tw[k1 * L];
+        v[r] = cmul(buf[k1 * (L + 1) + l], make_float2(t.x, -t.y));
+    }
+    fft_dit<R>(v);
+    const float inv_n = 1.f / (float)N;
+    float local_max = 0.f;
+    if (!MAX && a.given) {
+        a.ref = max_of_parts(a);
+        a.inv_ref = a.ref > 0.f ? 1.f / a.ref : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const float h1 = v[r].x * inv_n, h2 = v[r].y * inv_n;
+        const float e1 = __builtin_amdgcn_sqrtf(fmaf(x1[r], x1[r], h1 * h1));
+        const float e2 = __builtin_amdgcn_sqrtf(fmaf(x2[r], x2[r], h2 * h2));
+        if constexpr (MAX) {
+            local_max = fmaxf(local_max, fmaxf(e1, e2));     // (columns outside the image are 0)
+        } else if (a.given) {
+            if (has1) a.out[col * N + r * L + l] = compress_by_max(a, e1);
+            if (has2) a.out[(col + 1) * N + r * L + l] = compress_by_max(a, e2);
+        } else {
+            if (has1) store_env(a, col * N + r * L + l, e1, local_max);
+            if (has2) store_env(a, (col + 1) * N + r * L + l, e2, local_max);
+        }
+    }
+    if (!a.given) publish_max(a, local_max);
+}
+
 __global__ __launch_bounds__(256) void env_iq_kernel(EnvArgs a)
 {
     const long total = a.n_cols * a.N;
@@ -377,21 +703,31 @@ __global__ __launch_bounds__(256) void env_reduce_kernel(const float *part_max, 
     if (threadIdx.x == 0) *img_max = s[0];
 }
 
+// Compression by the image maximum: reduced by env_reduce_kernel, or, from at
+// most ENV_FEW_PARTS partial maxima, by every workgroup for itself (a launch
+// less).
 __global__ __launch_bounds__(256) void env_compress_kernel(EnvArgs a)
 {
     const long total = a.n_cols * a.N;
-    const float ref = *a.img_max;
-    const float inv_ref = ref > 0.f ? 1.f / ref : 0.f;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long)gridDim.x * 256) {
-        const float env = a.out[i];
-        float y;
-        if (ref > 0.f) {
-            y = compress_value(env, a.compress, inv_ref, a.param);
-        } else {   // all-zero image
-            y = a.compress == BF_COMPRESS_LOG ? -a.param : 0.f;
-        }
-        a.out[i] = y;
-    }
+    const long step = (long)gridDim.x * 256, first = (long)blockIdx.x * 256 + threadIdx.x;
+    // the thread's first two groups of four are loaded before the maxima
+    constexpr int F = 2;
+    float4 *o = reinterpret_cast<float4 *>(a.out);
+    const long groups = a.vec ? total / 4 : 0;
+    float4 y[F];
+#pragma unroll
+    for (int u = 0; u < F; ++u)
+        y[u] = first + u * step < groups ? o[first + u * step] : make_float4(0.f, 0.f, 0.f, 0.f);
+    a.ref = a.n_parts > 0 ? max_of_parts(a) : *a.img_max;
+    a.inv_ref = a.ref > 0.f ? 1.f / a.ref : 0.f;
+    auto value = [&](float v) { return compress_by_max(a, v); };
+    auto put = [&](long i, float4 v) { o[i] = make_float4(value(v.x), value(v.y), value(v.z), value(v.w)); };
+#pragma unroll
+    for (int u = 0; u < F; ++u)
+        if (first + u * step < groups) put(first + u * step, y[u]);
+    for (long i = first + F * step; i < groups; i += step) put(i, o[i]);
+    if (!a.vec)
+        for (long i = first; i < total; i += step) a.out[i] = value(a.out[i]);
 }
 
 }  // namespace bf
@@ -403,11 +739,15 @@ struct bf_env_s {
     long n_cols = 0;
     int N = 0, iq = 0, log2n = -1;
     long n_parts = 0;
-    int reg_m = 0;                // register FFT: M = N / 64 (0: not used)
+    int tile = 0;                 // tile FFT (N = 64, 128, 256)
+    int circ = 0;                 // circulant product on the matrix cores
+    int split = 1;                // workgroups a group of 16 columns is spread over
+    int waves = 1;                // wavefronts per workgroup of the tile FFT
+    int reg_m = 0;                // register FFT: M = N / 64 (N = 512, 1024)
     float2 wm[8] = {};
     float2 *d_tw = nullptr;
     float2 *d_tw_lane = nullptr;  // [6][64]
-    float2 *d_tw_mid = nullptr;   // [64][M]
+    float2 *d_tw_mid = nullptr;   // [64][M] or [R][L]
     float *d_q = nullptr;
     float *d_part = nullptr;      // [n_parts] per-workgroup maxima, then the maximum
     ~bf_env_s()
@@ -419,6 +759,28 @@ struct bf_env_s {
         if (d_part) (void)hipFree(d_part);
     }
 };
+
+// Lanes per pair of columns of the tile FFT (R = n / L values per lane).
+static int env_tile_lanes(int n) { return n <= 128 ? 8 : 16; }
+
+template <int R, int L>
+static void launch_tile(const EnvArgs &a, unsigned blocks, int waves, bool max_only, hipStream_t s)
+{
+    const size_t shm = (size_t)waves * EnvTile<R, L>::lds * sizeof(float2);
+    if (max_only)
+        hipLaunchKernelGGL((env_fft_tile_kernel<R, L, true>), dim3(blocks), dim3(64 * waves), shm, s, a);
+    else
+        hipLaunchKernelGGL((env_fft_tile_kernel<R, L, false>), dim3(blocks), dim3(64 * waves), shm, s, a);
+}
+
+static void launch_tile_n(const EnvArgs &a, unsigned blocks, int waves, bool max_only, hipStream_t s)
+{
+    switch (a.N) {
+        case 64: launch_tile<8, 8>(a, blocks, waves, max_only, s); break;
+        case 128: launch_tile<16, 8>(a, blocks, waves, max_only, s); break;
+        default: launch_tile<16, 16>(a, blocks, waves, max_only, s); break;
+    }
+}
 
 static bool live(bf_env e) { return e && e->magic == 0xBFE7E701u; }
 
@@ -450,12 +812,29 @@ int bf_env_create(int64_t n_cols, int32_t n, int32_t iq, bf_env *out)
     e->n_cols = n_cols;
     e->N = n;
     e->iq = iq;
-    // register FFT for 64 <= N <= 1024 (powers of two)
-    if (!iq && (n & (n - 1)) == 0 && n >= 64 && n <= 1024) e->reg_m = n / 64;
-    // workgroups of the envelope pass: one per column, four columns per
-    // workgroup (register FFT), or the grid-stride launch of the IQ path
-    e->n_parts = iq ? std::min<long>((n_cols * n + 255) / 256, 8192)
-                    : e->reg_m ? (n_cols + 7) / 8 : n_cols;
+    // workgroups of the envelope pass: the grid-stride launch of the IQ path,
+    // one per column, eight columns each (register FFT), 16 (circulant), or 2 * 64 / L columns per wavefront of the tile FFT (four
+    // wavefronts per workgroup, one where that leaves fewer workgroups than CUs)
+    if (!iq && (n & (n - 1)) == 0 && n >= 64 && n <= 256) {
+        e->tile = 1;
+        const long per_wave = 2 * (64 / env_tile_lanes(n));
+        const long waves = (n_cols + per_wave - 1) / per_wave;
+        e->waves = waves >= 4 * 256 ? 4 : 1;
+        e->n_parts = (waves + e->waves - 1) / e->waves;
+    } else if (!iq && (n == 512 || n == 1024)) {
+        e->reg_m = n / 64;
+        e->n_parts = (n_cols + 7) / 8;
+    } else {
+        e->circ = !iq && (n & (n - 1)) != 0 && n >= ENV_CIRC_MIN && n <= ENV_CIRC_MAX;
+        e->n_parts = iq ? std::min<long>((n_cols * n + 1023) / 1024, ENV_FEW_PARTS)
+                        : e->circ ? (n_cols + 15) / 16 : n_cols;
+        if (e->circ) {
+            const EnvCirc c = env_circ(n);
+            const long groups = e->n_parts;
+            e->split = groups >= 256 ? 1 : (int)std::min<long>((c.P * c.tiles + 3) / 4, 512 / groups);
+            e->n_parts = groups * e->split;
+        }
+    }
     hipError_t err = hipMalloc(&e->d_part, (e->n_parts + 1) * sizeof(float));
     if (err == hipSuccess && !iq) {
         if ((n & (n - 1)) == 0 && n >= 2) {
@@ -501,6 +880,19 @@ int bf_env_create(int64_t n_cols, int32_t n, int32_t iq, bf_env *out)
                 if (err == hipSuccess)
                     err = hipMemcpy(e->d_tw_lane, tl.data(), tl.size() * sizeof(float2),
                                     hipMemcpyHostToDevice);
+                if (err == hipSuccess)
+                    err = hipMemcpy(e->d_tw_mid, tm.data(), tm.size() * sizeof(float2),
+                                    hipMemcpyHostToDevice);
+            }
+            if (err == hipSuccess && e->tile) {
+                const int L = env_tile_lanes(n), R = n / L;
+                std::vector<float2> tm(n);
+                for (int l = 0; l < L; ++l)
+                    for (int k = 0; k < R; ++k) {
+                        const double ph = -2.0 * M_PI * (double)(l * k) / n;
+                        tm[(size_t)k * L + l] = make_float2((float)cos(ph), (float)sin(ph));
+                    }
+                err = hipMalloc(&e->d_tw_mid, tm.size() * sizeof(float2));
                 if (err == hipSuccess)
                     err = hipMemcpy(e->d_tw_mid, tm.data(), tm.size() * sizeof(float2),
                                     hipMemcpyHostToDevice);
@@ -572,29 +964,53 @@ int bf_envelope(bf_env e, const float *img, float *out, int32_t compress, double
     hipStream_t s = (hipStream_t)stream;
     const bool two_pass = compress != BF_COMPRESS_NONE && ref <= 0.0;
     const long total = e->n_cols * e->N;
-    const unsigned eblocks = (unsigned)std::min<long>((total + 255) / 256, 8192);
+    a.n_parts = e->n_parts <= ENV_FEW_PARTS ? (int)e->n_parts : 0;
+    a.given = 0;
+    // From 2^21 points on the tile FFT runs twice, first for the maximum alone,
+    // instead of storing the envelope and reading it back: the 128 x 128 x 256
+    // volume moves 50 MB instead of 67 (22.5 -> 17.8 us); smaller images are
+    // bound by the latency of a pass.
+    const bool twice = e->tile && two_pass && a.n_parts > 0 && total >= (1L << 21);
+    a.vec = total % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     if (e->iq) {
-        hipLaunchKernelGGL(env_iq_kernel, dim3(eblocks), dim3(256), 0, s, a);
-    } else if (e->reg_m) {
-        const dim3 g((unsigned)((e->n_cols + 7) / 8)), b(256);
-        switch (e->reg_m) {
-            case 1: hipLaunchKernelGGL(env_fft_reg_kernel<1>, g, b, 0, s, a); break;
-            case 2: hipLaunchKernelGGL(env_fft_reg_kernel<2>, g, b, 0, s, a); break;
-            case 4: hipLaunchKernelGGL(env_fft_reg_kernel<4>, g, b, 0, s, a); break;
-            case 8: hipLaunchKernelGGL(env_fft_reg_kernel<8>, g, b, 0, s, a); break;
-            default: hipLaunchKernelGGL(env_fft_reg_kernel<16>, g, b, 0, s, a); break;
+        hipLaunchKernelGGL(env_iq_kernel, dim3((unsigned)e->n_parts), dim3(256), 0, s, a);
+    } else if (e->tile) {
+        const unsigned g = (unsigned)e->n_parts;
+        launch_tile_n(a, g, e->waves, twice, s);
+        if (twice) {
+            a.given = 1;
+            launch_tile_n(a, g, e->waves, false, s);
         }
+    } else if (e->reg_m) {
+        const dim3 g((unsigned)e->n_parts), b(256);
+        if (e->reg_m == 8)
+            hipLaunchKernelGGL(env_fft_reg_kernel<8>, g, b, 0, s, a);
+        else
+            hipLaunchKernelGGL(env_fft_reg_kernel<16>, g, b, 0, s, a);
     } else if (e->log2n > 0) {
         const int T = std::min(256, std::max(64, e->N / 2));
         hipLaunchKernelGGL(env_fft_kernel, dim3((unsigned)e->n_cols), dim3(T),
                            (size_t)e->N * 8, s, a);
+    } else if (e->circ) {
+        const EnvCirc c = env_circ(e->N);
+        const size_t shm = env_circ_lds(c);
+        if (shm > 65536) {
+            const hipError_t he = hipFuncSetAttribute(reinterpret_cast<const void *>(&env_circ_kernel),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+            if (he != hipSuccess) return hip_fail(he, "envelope LDS size");
+        }
+        hipLaunchKernelGGL(env_circ_kernel, dim3((unsigned)(e->n_parts / e->split), e->split), dim3(256),
+                           shm, s, a, c);
     } else {
         hipLaunchKernelGGL(env_direct_kernel, dim3((unsigned)e->n_cols), dim3(256),
                            (size_t)3 * e->N * sizeof(float), s, a);
     }
-    if (two_pass) {
-        hipLaunchKernelGGL(env_reduce_kernel, dim3(1), dim3(256), 0, s, e->d_part, e->n_parts,
-                           e->d_part + e->n_parts);
+    if (two_pass && !twice) {
+        if (a.n_parts == 0)
+            hipLaunchKernelGGL(env_reduce_kernel, dim3(1), dim3(256), 0, s, e->d_part, e->n_parts,
+                               e->d_part + e->n_parts);
+        const long items = a.vec ? total / 4 : total;
+        const unsigned eblocks = (unsigned)std::min<long>((items + 511) / 512, 2048);
         hipLaunchKernelGGL(env_compress_kernel, dim3(eblocks), dim3(256), 0, s, a);
     }
     hipError_t err = hipGetLastError();

@@ -29,17 +29,44 @@
 
 namespace bf {
 
-__device__ inline uint32_t load_pair(const int16_t *rf, long row, int t, int S, bool even_S)
+// Pairs of samples in one access at any alignment of the row: with an odd
+// sample count every other row starts 2 (loads) or 4 (stores) bytes off the
+// access size, which global memory accesses allow; two half-size accesses per
+// pair made the decode of 20 x 127 x 1501 samples to BF16 take 15.2 us, 8 now.
+typedef uint32_t pair_u32 __attribute__((aligned(2)));
+typedef unsigned long long pair_u64 __attribute__((aligned(4)));
+
+// Samples t and t + 1 of the rows of 16 transmits k0 .. k0 + 15 of channel j, each
+// packed as (x[t] | x[t+1] << 16).  No lane branches around a load, so that all
+// are in flight (a branch per load had put a wait behind each): transmits past
+// n_tx read the last row (their column of the operand H^T is zero), a lane past
+// the row reads a pair whose result is not stored, and the last sample of an odd
+// row is the upper half of the pair before it.
+__device__ inline void load_pairs(const DecodeArgs &a, int kb, int g, int j, int t, uint32_t (&d)[16])
 {
-    // Samples t and t+1 of one trace packed as (x[t] | x[t+1] << 16).
     // (global view: the persistent kernel reads rf from a pointer table)
-    const gptr<int16_t> p = as_global(rf + row * (long)S + t);
-    if (even_S) {
-        return (t < S) ? *reinterpret_cast<gptr<uint32_t>>(p) : 0u;
+    const int at = min(t, a.S - 2), shift = t == a.S - 1 ? 16 : 0;
+    const int k0 = kb * 32 + 16 * g;
+    const long stride = (long)a.n_ch * a.S;
+    const int16_t *p = a.rf + (long)j * a.S + at;
+    if (kb * 32 + 32 <= a.n_tx) {        // (uniform: 16 rows a uniform stride apart)
+        p += k0 * stride;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) d[u] = *reinterpret_cast<gptr<pair_u32>>(as_global(p + u * stride));
+    } else {
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            d[u] = *reinterpret_cast<gptr<pair_u32>>(as_global(p + min(k0 + u, a.n_tx - 1) * stride));
     }
-    uint32_t a = (t < S) ? (uint16_t)p[0] : 0u;
-    uint32_t b = (t + 1 < S) ? (uint16_t)p[1] : 0u;
-    return a | (b << 16);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) d[u] >>= shift;
+}
+// (rows of one sample)
+__device__ inline void load_singles(const DecodeArgs &a, int k0, int j, uint32_t (&d)[16])
+{
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+        d[u] = (uint16_t)as_global(a.rf + (long)min(k0 + u, a.n_tx - 1) * a.n_ch + j)[0];
 }
 
 __device__ inline uint32_t pick_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3, int sh)
@@ -56,31 +83,25 @@ __device__ inline uint32_t f32_to_bf16_rne(float f)
 }
 
 template <int OT>
-__device__ inline void store_pair(void *e, long idx, int v0, int v1, bool two, bool even_S)
+__device__ inline void store_pair(void *e, long idx, int v0, int v1, bool two)
 {
-    // (with an even sample count the pair is 8-byte aligned: one 8-byte store
-    // per lane, so each half-wavefront writes 256 contiguous bytes in one
-    // instruction)
+    // (one store per lane, so each half-wavefront writes 256 contiguous bytes
+    // in one instruction)
     if constexpr (OT == ET_F32 || OT == ET_I32) {
         const uint32_t u0 = OT == ET_F32 ? __float_as_uint((float)v0) : (uint32_t)v0;
         const uint32_t u1 = OT == ET_F32 ? __float_as_uint((float)v1) : (uint32_t)v1;
         const gptr_mut<uint32_t> p = as_global_mut(static_cast<uint32_t *>(e) + idx);
-        if (two && even_S) {
-            *reinterpret_cast<gptr_mut<unsigned long long>>(p) =
-                (unsigned long long)u0 | ((unsigned long long)u1 << 32);
-        } else {
+        if (two)
+            *reinterpret_cast<gptr_mut<pair_u64>>(p) = (unsigned long long)u0 | ((unsigned long long)u1 << 32);
+        else
             p[0] = u0;
-            if (two) p[1] = u1;
-        }
     } else {
         const gptr_mut<uint16_t> p = as_global_mut(static_cast<uint16_t *>(e) + idx);
         uint32_t b0 = f32_to_bf16_rne((float)v0), b1 = f32_to_bf16_rne((float)v1);
-        if (two && even_S) {
-            *reinterpret_cast<gptr_mut<uint32_t>>(p) = b0 | (b1 << 16);
-        } else {
+        if (two)
+            *reinterpret_cast<gptr_mut<pair_u32>>(p) = b0 | (b1 << 16);
+        else
             p[0] = (uint16_t)b0;
-            if (two) p[1] = (uint16_t)b1;
-        }
     }
 }
 
@@ -93,23 +114,21 @@ __device__ inline void decode_item(const DecodeArgs &a, const v4i *lds_A, const 
 {
     const int n = lane & 31, g = lane >> 5;
     const int t = chunk * 64 + 2 * n;
-    const bool even_S = (a.S & 1) == 0;
-
     v4i bhe[KB], bho[KB], ble[KB], blo[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
+        uint32_t d[16];
+        if (a.S > 1)
+            load_pairs(a, kb, g, j, t, d);
+        else
+            load_singles(a, kb * 32 + 16 * g, j, d);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            uint32_t d[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = kb * 32 + 16 * g + 4 * c + u;
-                d[u] = (k < a.n_tx) ? load_pair(a.rf, (long)k * a.n_ch + j, t, a.S, even_S) : 0u;
-            }
-            bhe[kb][c] = (int)pick_bytes(d[0], d[1], d[2], d[3], 8);
-            bho[kb][c] = (int)pick_bytes(d[0], d[1], d[2], d[3], 24);
-            ble[kb][c] = (int)(pick_bytes(d[0], d[1], d[2], d[3], 0) ^ 0x80808080u);
-            blo[kb][c] = (int)(pick_bytes(d[0], d[1], d[2], d[3], 16) ^ 0x80808080u);
+            const uint32_t *q = d + 4 * c;
+            bhe[kb][c] = (int)pick_bytes(q[0], q[1], q[2], q[3], 8);
+            bho[kb][c] = (int)pick_bytes(q[0], q[1], q[2], q[3], 24);
+            ble[kb][c] = (int)(pick_bytes(q[0], q[1], q[2], q[3], 0) ^ 0x80808080u);
+            blo[kb][c] = (int)(pick_bytes(q[0], q[1], q[2], q[3], 16) ^ 0x80808080u);
         }
     }
 
@@ -138,7 +157,7 @@ __device__ inline void decode_item(const DecodeArgs &a, const v4i *lds_A, const 
                 if (m < a.n_tx) {
                     const int corr = 128 * lds_cs[m];
                     store_pair<OT>(a.e, ((long)m * a.n_ch + j) * a.S + t, ce[r] + corr,
-                                   co[r] + corr, two, even_S);
+                                   co[r] + corr, two);
                 }
             }
         }

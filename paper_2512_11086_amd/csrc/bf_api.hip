@@ -341,6 +341,7 @@ int Frame::init(const bf_params &src)
         hipError_t he = hipMemcpy(d_hann, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
         if (he != hipSuccess) return hip_fail(he, "upload of the Hann table");
     }
+    choose_box();
     choose_groups();
     if (groups > 1) {
         d_part = (float *)alloc((size_t)groups * out_elems() * sizeof(float));
@@ -360,6 +361,51 @@ int Frame::init(const bf_params &src)
             hipSuccess)
         return hip_fail(e, "upload of plan tables");
     return BF_OK;
+}
+
+// Lane tile and workgroup shape of a HERCULES plan: 12 wavefronts as 16 x 16 x
+// 3 depths (times the points per lane) by default.  Another shape is taken
+// where it needs clearly less work on this grid, by the vector instructions of
+// a workgroup per trace: 15 per point for the delay, the weight and the address
+// plus 4 per (mirror) point for the read (IQ 35 and 10), about 15 per staged
+// pair of quads, and 250 per wavefront and batch.  The padded points of ragged
+// grids and of mirrored halves decide mostly.  us, default and chosen:
+// 48 x 48 x 96 from 64 x 128 traces 932, 851; 49 x 109 x 120 from 24 x 128 1 290,
+// 1 160; IQ 32 x 24 x 144 from 20 x 116 376, 300; IQ 118 x 128 x 71 from 20 x 64
+// 969, 846.  The count is good to about 5 %, so a shape has to be 6 % better.
+void Frame::choose_box()
+{
+    if (p.mode != BF_HERCULES_3D || variant == BF_DAS_GATHER || p.interp == BF_INTERP_NEAREST) return;
+    const int tiles[3][3] = {{3, 3, 0}, {2, 3, 1}, {3, 2, 1}};
+    const int blocks[3][3] = {{2, 2, 3}, {3, 2, 2}, {2, 1, 6}};
+    const int lx0 = lx, ly0 = ly, lz0 = lz, bw0[3] = {bw[0], bw[1], bw[2]};
+    double best = 1e300, first = 1e300;
+    int bt = 0, bb = 0;
+    for (int t = 0; t < 3; ++t)
+        for (int b = 0; b < 3; ++b) {
+            set_tile(tiles[t][0], tiles[t][1], tiles[t][2]);
+            for (int r = 0; r < 3; ++r) bw[r] = blocks[b][r];
+            LdsCfg c;
+            if (!lds_config(das_args(nullptr, nullptr, p.c), &c)) continue;
+            const int nm = mirror_copies(c.mir), waves = bw[0] * bw[1] * bw[2];
+            const double terms = (double)waves * c.zp * (p.iq ? 35 + 10 * nm : 15 + 4 * nm);
+            const double staging = 15.0 / 64.0 * nm * c.lmax * (p.iq ? 2 : 1);
+            const double cost = (double)c.blocks_x * c.blocks_y * c.blocks_z *
+                                (terms + staging + 250.0 * waves / c.nb);
+            if (t == 0 && b == 0) first = cost;
+            if (cost < best) {
+                best = cost;
+                bt = t;
+                bb = b;
+            }
+        }
+    if (best < 0.94 * first) {
+        set_tile(tiles[bt][0], tiles[bt][1], tiles[bt][2]);
+        for (int r = 0; r < 3; ++r) bw[r] = blocks[bb][r];
+    } else {
+        set_tile(lx0, ly0, lz0);
+        for (int r = 0; r < 3; ++r) bw[r] = bw0[r];
+    }
 }
 
 // Channel groups: small grids give too few workgroups to fill 256 CUs, so the

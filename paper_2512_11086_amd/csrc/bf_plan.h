@@ -53,6 +53,7 @@ struct Frame {
     int init(const bf_params &src);
     void set_tile(int lx, int ly, int lz);
     void find_mirrors();
+    void choose_box();
     void choose_groups();
     int64_t e_elems() const;
     int64_t out_elems() const;

@@ -47,6 +47,8 @@ def _both(torch, desc, e, axes, e_type="f32"):
     out = []
     for allowed in (3, 0):
         plan = bfm.Plan(desc, None, e_type=e_type)
+        plan.set_tile(3, 3, 0)           # 16 x 16 x 3 points per box, which decides the axes
+        plan.set_das_config("lds", (2, 2, 3), 48)
         used = _lib.lib().bf_test_set_mirrors(plan._h, allowed)
         assert used == (axes & allowed)
         out.append(plan.das(e).cpu().numpy())

@@ -568,23 +568,24 @@ int Frame::decode(const int16_t *rf, void *e, hipStream_t s) const
 // (the direct-gather kernel is used then).
 // Dynamic LDS of one workgroup: the device's per-block limit, at most 80 KiB
 // so that two workgroups share a CU's 160 KiB.
-static size_t lds_cap_bytes()
+static size_t lds_cap_bytes(size_t most = 80 * 1024)
 {
-    static const size_t cap = [] {
+    static const size_t device = [] {
         int dev = 0, v = 0;
         (void)hipGetDevice(&dev);
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
             v <= 0)
             v = 64 * 1024;
-        return std::min<size_t>((size_t)v, 80 * 1024);
+        return (size_t)v;
     }();
-    return cap;
+    return std::min(device, most);
 }
 
 // adj: the adjoint's LDS layout (1: dL/dc, 2: dL/de, 3: both), 0 for DAS.
 // The wavefront tile is a's; bw_adj (if set) replaces the plan's workgroup
 // shape.
-bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj) const
+// solo: a launch of its own (bf_das), whose workgroups may take a whole CU each.
+bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj, bool solo) const
 {
     const bool sep = p.mode != BF_HERCULES_3D;   // separable: FORCES, TPW, VLS
     const int *bw = bw_adj ? bw_adj : this->bw;
@@ -694,6 +695,19 @@ bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj
                            lds_bytes(p.n_tx, p.n_ch, nbb, lmax, qs, guard, adj, p.mode, nm) > lds_cap))
         nbb -= unit;
     if (nbb < unit || nthr > 1024) return false;
+    // A launch with at most one workgroup per CU (a small plane, a row-column
+    // volume of few points) fills larger batches: each batch costs the latency
+    // of its loads and a barrier, which nothing else on the CU covers (128 x 128
+    // points from 32 x 32 traces: 36 us with batches of 8 traces, 32 with 16).
+    // (which kernel runs is decided by the shared cap alone)
+    const long wgs = (long)((cfg->ex + tx - 1) / tx) * ((cfg->ey + ty - 1) / ty) *
+                     ((grid.nz + z_off + tz - 1) / tz) * a.groups;
+    if (solo && sep && adj == 0 && wgs <= 256) {
+        const size_t whole = lds_cap_bytes(152 * 1024);
+        while (nbb + unit <= nb && rounds(nbb + unit) <= max_rounds &&
+               lds_bytes(p.n_tx, p.n_ch, nbb + unit, lmax, qs, guard, adj, p.mode, nm) <= whole)
+            nbb += unit;
+    }
     cfg->bwx = bw[0];
     cfg->bwy = bw[1];
     cfg->bwz = bw[2];
@@ -769,7 +783,7 @@ int Frame::das(const void *e, float *out, double c, hipStream_t s, float *part) 
     if (part) a.part = part;
     LdsCfg cfg;
     hipError_t err;
-    if (variant != BF_DAS_GATHER && lds_config(a, &cfg))
+    if (variant != BF_DAS_GATHER && lds_config(a, &cfg, 0, nullptr, true))
         err = launch_das_lds(a, cfg, p.mode, das_et(), p.interp, s);
     else
         err = launch_das(a, p.mode, das_et(), p.interp, s);
@@ -1005,7 +1019,7 @@ int bf_plan_get_info(bf_plan plan, bf_plan_info *info)
         // the kernel bf_das actually runs (LDS windows may not fit: gather)
         LdsCfg cfg;
         const bool lds = f.variant != BF_DAS_GATHER &&
-                         f.lds_config(f.das_args(nullptr, nullptr, f.p.c), &cfg);
+                         f.lds_config(f.das_args(nullptr, nullptr, f.p.c), &cfg, 0, nullptr, true);
         const bool z2 = lds && (cfg.zp == 2 || (cfg.mir && f.variant == BF_DAS_LDS_Z2 && f.z2_ok()));
         info->variant = lds ? (z2 ? BF_DAS_LDS_Z2 : BF_DAS_LDS) : BF_DAS_GATHER;
         info->nb = lds ? cfg.nb * mirror_copies(cfg.mir) : f.nb;

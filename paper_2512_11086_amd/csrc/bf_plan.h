@@ -61,7 +61,8 @@ struct Frame {
     size_t e_bytes() const;
     DecodeArgs decode_args(const int16_t *rf, void *e) const;
     DasArgs das_args(const void *e, float *out, double c) const;
-    bool lds_config(const DasArgs &a, LdsCfg *cfg, int adj = 0, const int *bw_adj = nullptr) const;
+    bool lds_config(const DasArgs &a, LdsCfg *cfg, int adj = 0, const int *bw_adj = nullptr,
+                    bool solo = false) const;
     void adjoint_e_tile(DasArgs *a, int bw_out[3]) const;   // the RF gradient's lane tile
     bool z2_ok() const;          // two depth points per lane apply to this frame
     int decode(const int16_t *rf, void *e, hipStream_t s) const;

@@ -421,7 +421,8 @@ int bf_demodulate(bf_demod d, const int16_t *rf, void *iq, void *stream);
  * power-of-two n from 64 to 1024 a register-resident FFT per pair of columns
  * (two real columns as one complex transform: the inverse DFT of
  * -j sgn(k) DFT(x1 + j x2) is H{x1} + j H{x2}, and env = sqrt(x^2 + H{x}^2));
- * other powers of two a radix-2 FFT in LDS; a direct circular sum otherwise.
+ * other powers of two a radix-2 FFT in LDS; other n from 24 to 1000 a circulant
+ * product on the matrix cores; a direct circular sum otherwise.
  * A plan holds its tables and a partial-maximum buffer, so calls of one plan
  * must not overlap on the device.
  * ------------------------------------------------------------------------- */

@@ -174,8 +174,9 @@ static int build_batch(bf_plan plan)
         } else if (groups[f] > 1 &&
                    (long)c.blocks_x * c.blocks_y * c.blocks_z * fr.adj_groups >= 2L * cus0) {
             // A frame of a class that would need the channel split, whose own
-            // launch (the single-frame kernel with the frame's channel groups)
-            // already gives two workgroups per CU: that launch, captured in
+            // launch (the single-frame kernel) gives two workgroups per CU
+            // already with the groups that fill the chip once (adj_groups; the
+            // forward launch may split further): that launch, captured in
             // the pass like the others, measured faster than its share of the
             // persistent launch (a pair of 256 x 256 planes from 128 x 128
             // traces: 1.35 ms per pass persistent).

@@ -422,12 +422,21 @@ void Frame::choose_box()
 //    traces (64 boxes): m = 1, 2, 4 run 131, 123, 155 us; 181 x 303 points,
 //    127 rows (57 boxes): 132, 127, 145 us, and 149 with the 10 groups of the
 //    floor.
-//  - Volumes aim at five workgroups per slot (HERCULES) or three (TPW, VLS,
-//    whose groups end in partial chunks): HERCULES 61 x 53 x 97 points from 24
-//    x 100 traces 764 us with 2 groups, 627 with 10; IQ 64 x 64 x 128 from 64 x
-//    64 traces 2 090 us with 1, 1 020 with 8.  A group keeps at least 192
-//    traces and two rows (eight in the separable modes): below that the
-//    partial images cost more than the balance gains.
+//    Planes of FP32 data keep the floor: they are the autofocus' planes, whose
+//    dL/dc is the small rest of a sum that cancels and shows every change of
+//    the image's rounding.
+//  - TPW and VLS volumes weigh whole chunks likewise: a group costs its m
+//    chunks and a setup that shrinks with the transmits, a launch its
+//    workgroups per slot and 0.4 for the last, partly filled one; a split has
+//    to be 5 % better by this count than none.  VLS 44 x 34 x 195 points from
+//    44 x 64 traces (594 boxes), G = 1, 2, 3, 4, 8: 570, 539, 564, 501, 511 us;
+//    TPW 37 x 27 x 147 from 32 x 64 (294 boxes), 1, 2, 4, 5, 8: 258, 238, 199,
+//    232, 205; 102 x 76 x 121 from 24 x 32 (1435 boxes), 1, 2: 285, 291.
+//  - HERCULES volumes aim at five workgroups per slot: 61 x 53 x 97 points from
+//    24 x 100 traces 764 us with 2 groups, 627 with 10; IQ 64 x 64 x 128 from 64
+//    x 64 traces 2 090 us with 1, 1 020 with 8.  A group keeps at least 192
+//    traces and two rows: below that the partial images cost more than the
+//    balance gains.
 // The partial images stay within BF_DAS_NOALLOC_MAX_BYTES.
 void Frame::choose_groups()
 {
@@ -442,9 +451,10 @@ void Frame::choose_groups()
     const long slots = 512;
     const long cap = std::max<long>(1, BF_DAS_NOALLOC_MAX_BYTES / (out_elems() * (long)sizeof(float)));
     long G = 1;
+    const int chunks = (p.n_ch + JC - 1) / JC;
     if (p.mode == BF_FORCES_2D) {
+        if (p.e_type == BF_E_F32 && !p.iq) return;
         double best = 1e300;
-        const int chunks = (p.n_ch + JC - 1) / JC;
         for (int m = 1; m <= chunks; ++m) {
             const long g = (chunks + m - 1) / m;
             if (g > cap || g > gmax) continue;
@@ -458,10 +468,24 @@ void Frame::choose_groups()
         groups = (int)G;
         return;
     }
-    const bool herc = p.mode == BF_HERCULES_3D;
-    G = herc ? (5 * slots + boxes - 1) / boxes : (3 * slots + boxes / 2) / boxes;
+    if (p.mode != BF_HERCULES_3D) {
+        const double setup = 0.1 + 8.0 / p.n_tx;
+        double best = 0.95 * ((double)boxes / slots + 0.4) * (chunks + setup);
+        for (int m = 2; m < chunks; ++m) {
+            const long g = (chunks + m - 1) / m;
+            if (g > cap || g > gmax || g > 16) continue;
+            const double cost = ((double)(boxes * g) / slots + 0.4) * (m + setup);
+            if (cost < best) {
+                best = cost;
+                G = g;
+            }
+        }
+        groups = (int)G;
+        return;
+    }
+    G = (5 * slots + boxes - 1) / boxes;
     G = std::min(G, (long)p.n_tx * p.n_ch / 192);
-    G = std::min(G, (long)p.n_ch / (herc ? 2 : 8));
+    G = std::min(G, (long)p.n_ch / 2);
     groups = (int)std::max<long>(adj_groups, std::min<long>(std::min<long>(G, 16), cap));
 }
 

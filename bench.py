@@ -91,7 +91,16 @@ def active_terms(desc, dev) -> int:
     return total
 
 
-def algorithmic_flops(desc, n_act: int, iq: bool = False, adjoint_c: bool = False) -> float:
+def mirror_copies(plan) -> int:
+    """Points that share a term's delay and weight in the plan's DAS launch
+    (mirror points: 1, 2 or 4)."""
+    from paper_2512_11086_amd import _lib
+    axes = _lib.lib().bf_test_set_mirrors(plan._h, 3)     # (3: every axis stays allowed)
+    return {0: 1, 1: 2, 2: 2, 3: 4}[axes]
+
+
+def algorithmic_flops(desc, n_act: int, iq: bool = False, adjoint_c: bool = False,
+                      copies: int = 1) -> float:
     """FP32 flops (FMA = 2; a floor, fract, square root or reciprocal = 1) of
     one DAS launch (or its dL/dc adjoint) with n_act active terms
     (apodization > 0), counted as the kernels evaluate each term.  The cubic
@@ -103,7 +112,8 @@ def algorithmic_flops(desc, n_act: int, iq: bool = False, adjoint_c: bool = Fals
     Per active term: HERCULES (one receive path per term) delay 12 (dx,
     rho^2, (d/k)^2, sqrt, d/k + z/k, rcp, fma, floor, fract) + apodization 4
     (the Hann table: scale, floor, and one fma from the entry's base and
-    slope); FORCES, TPW and
+    slope), formed once for the `copies` mirror points that share them (IQ:
+    with the phase and the weighted rotation, 7); FORCES, TPW and
     VLS separate the path into a transmit part per (point, transmit)
     (FORCES distance to the column 8, TPW x sin + z (cos - 1) 4, VLS signed
     distance to the line 11) and a receive part with its weight per active
@@ -122,7 +132,8 @@ def algorithmic_flops(desc, n_act: int, iq: bool = False, adjoint_c: bool = Fals
     else:
         per_term = 6 + 2
     if mode == "hercules":
-        return n_act * (12 + 4 + per_term) + coef
+        shared = 12 + 4 + (7 if iq else 0)
+        return n_act * (shared / copies + per_term - (7 if iq else 0)) + coef
     n_tx = desc["n_tx"]
     n_pts = int(np.prod(desc["dims"]))
     f_tx = {"forces": 8, "tpw": 4, "vls": 11}[mode]
@@ -597,7 +608,7 @@ def iq_pipeline(torch, bfm, synth, desc, H, rf_d, n_act, reps: int):
     dem_flops = n_tr * n_out * (2 * parts + 6)
     dem_bytes = n_tr * (2 * desc["n_samples"] + 4 * n_out)
     dem_tf = dem_flops / (dem_ms * 1e-3) / 1e12
-    das_tf = algorithmic_flops(dq, n_act, iq=True) / (das_ms * 1e-3) / 1e12
+    das_tf = algorithmic_flops(dq, n_act, iq=True, copies=mirror_copies(plan)) / (das_ms * 1e-3) / 1e12
     nominal = int(np.prod(dq["dims"])) * dq["n_tx"] * dq["n_ch"]
     return {
         "workload": "same RF -> demodulate (36-tap low-pass, D = 2, fd = 7.5 MHz) -> "
@@ -748,7 +759,7 @@ def n4_workloads(torch, bfm, synth, reps: int = 6):
         dec_ms = ev[0].elapsed_time(ev[1]) / reps
         das_ms = ev[1].elapsed_time(ev[2]) / reps
         n_act = active_terms(desc, dev)
-        tf = algorithmic_flops(desc, n_act) / (das_ms * 1e-3) / 1e12
+        tf = algorithmic_flops(desc, n_act, copies=mirror_copies(plan)) / (das_ms * 1e-3) / 1e12
         nominal = int(np.prod(desc["dims"])) * desc["n_tx"] * desc["n_ch"]
         res[name] = {"n_tx": desc["n_tx"], "decode_ms": round(dec_ms, 4),
                      "das_ms": round(das_ms, 3),
@@ -889,7 +900,7 @@ def main():
     value = nominal / (ms_step * 1e-3) / 1e9
     n_act = active_terms(desc, dev)
     # algorithmic FP32 work of the launch (algorithmic_flops)
-    achieved = algorithmic_flops(desc, n_act) / (das_ms * 1e-3) / 1e12
+    achieved = algorithmic_flops(desc, n_act, copies=mirror_copies(plan)) / (das_ms * 1e-3) / 1e12
     dec_bytes = rf.size * 2 + rf.size * 4
     res = {
         "metric": "G voxel*tx*ch samples/s (+ volumes/s), decode + DAS at oracle accuracy",

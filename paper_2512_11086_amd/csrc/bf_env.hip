@@ -230,7 +230,9 @@ __global__ __launch_bounds__(256) void env_direct_kernel(EnvArgs a)
 // 181, 45.
 //
 // Few columns (less than a workgroup per CU) spread their tiles over several
-// workgroups, which then store their outputs from the accumulators.
+// workgroups, which then store their outputs from the accumulators; every one
+// of them reads whole columns, so an envelope that overwrites its image keeps
+// one workgroup per group of columns.
 //
 // LDS: the columns by phase ([16][stride], phase pe at pe H4; stride = 4 modulo
 // 64 words, so 16 columns x 4 samples fall in different banks), their
@@ -741,7 +743,7 @@ struct bf_env_s {
     long n_parts = 0;
     int tile = 0;                 // tile FFT (N = 64, 128, 256)
     int circ = 0;                 // circulant product on the matrix cores
-    int split = 1;                // workgroups a group of 16 columns is spread over
+    int split = 1;                // workgroups a group of 16 columns is spread over (out apart from img)
     int waves = 1;                // wavefronts per workgroup of the tile FFT
     int reg_m = 0;                // register FFT: M = N / 64 (N = 512, 1024)
     float2 wm[8] = {};
@@ -964,7 +966,10 @@ int bf_envelope(bf_env e, const float *img, float *out, int32_t compress, double
     hipStream_t s = (hipStream_t)stream;
     const bool two_pass = compress != BF_COMPRESS_NONE && ref <= 0.0;
     const long total = e->n_cols * e->N;
-    a.n_parts = e->n_parts <= ENV_FEW_PARTS ? (int)e->n_parts : 0;
+    const bool apart = out + total <= img || img + total <= out;
+    const int split = apart ? e->split : 1;
+    const long n_parts = e->n_parts / e->split * split;      // (split divides n_parts)
+    a.n_parts = n_parts <= ENV_FEW_PARTS ? (int)n_parts : 0;
     a.given = 0;
     // From 2^21 points on the tile FFT runs twice, first for the maximum alone,
     // instead of storing the envelope and reading it back: the 128 x 128 x 256
@@ -999,7 +1004,7 @@ int bf_envelope(bf_env e, const float *img, float *out, int32_t compress, double
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
             if (he != hipSuccess) return hip_fail(he, "envelope LDS size");
         }
-        hipLaunchKernelGGL(env_circ_kernel, dim3((unsigned)(e->n_parts / e->split), e->split), dim3(256),
+        hipLaunchKernelGGL(env_circ_kernel, dim3((unsigned)(n_parts / split), split), dim3(256),
                            shm, s, a, c);
     } else {
         hipLaunchKernelGGL(env_direct_kernel, dim3((unsigned)e->n_cols), dim3(256),
@@ -1007,7 +1012,7 @@ int bf_envelope(bf_env e, const float *img, float *out, int32_t compress, double
     }
     if (two_pass && !twice) {
         if (a.n_parts == 0)
-            hipLaunchKernelGGL(env_reduce_kernel, dim3(1), dim3(256), 0, s, e->d_part, e->n_parts,
+            hipLaunchKernelGGL(env_reduce_kernel, dim3(1), dim3(256), 0, s, e->d_part, n_parts,
                                e->d_part + e->n_parts);
         const long items = a.vec ? total / 4 : total;
         const unsigned eblocks = (unsigned)std::min<long>((items + 511) / 512, 2048);

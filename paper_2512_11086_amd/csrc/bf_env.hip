@@ -234,6 +234,11 @@ __global__ __launch_bounds__(256) void env_direct_kernel(EnvArgs a)
 // of them reads whole columns, so an envelope that overwrites its image keeps
 // one workgroup per group of columns.
 //
+// A column with an infinite or NaN sample has no finite envelope: where the
+// zeros of q keep such a sample out of half of the products, every output of
+// the column gets 1e-30 times the column's sum added (nothing beside finite
+// values, as the rounded zeros of a summed q would be).
+//
 // LDS: the columns by phase ([16][stride], phase pe at pe H4; stride = 4 modulo
 // 64 words, so 16 columns x 4 samples fall in different banks), their
 // envelopes (same shape), and q by distance: entry d + H4 + 3 holds the q of
@@ -264,6 +269,7 @@ static size_t env_circ_lds(const EnvCirc &c) { return ((size_t)2 * 16 * c.stride
 __global__ __launch_bounds__(256) void env_circ_kernel(EnvArgs a, EnvCirc c)
 {
     extern __shared__ float sf[];
+    __shared__ float s_rest[16];
     float *xs = sf, *env = sf + 16 * c.stride, *qs = env + 16 * c.stride;
     const int N = a.N, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long col0 = (long)blockIdx.x * 16;
@@ -279,12 +285,20 @@ __global__ __launch_bounds__(256) void env_circ_kernel(EnvArgs a, EnvCirc c)
     }
     __syncthreads();
     const float *img = a.img + col0 * N;
-    for (int g = wave; g < cols; g += 4)
-        for (int n = lane; n < N; n += 64)
-            xs[g * c.stride + (c.P == 2 ? (n & 1) * c.H4 + (n >> 1) : n)] = img[(long)g * N + n];
+    for (int g = wave; g < cols; g += 4) {
+        float rest = 0.f;
+        for (int n = lane; n < N; n += 64) {
+            const float x = img[(long)g * N + n];
+            xs[g * c.stride + (c.P == 2 ? (n & 1) * c.H4 + (n >> 1) : n)] = x;
+            rest = fmaf(x, 1e-30f, rest);
+        }
+        for (int d = 32; d > 0; d >>= 1) rest += __shfl_xor(rest, d, 64);
+        if (lane == 0) s_rest[g] = rest;
+    }
     __syncthreads();
     const int col = lane & 15, kq = lane >> 4;
     const int total = c.P * c.tiles;
+    const float rest = col < cols ? s_rest[col] : 0.f;
     float local_max = 0.f;
     for (int t = blockIdx.y * 4 + wave; t < total; t += 4 * gridDim.y) {
         const int ph = t / c.tiles;                         // parity of the outputs (P = 2)
@@ -310,7 +324,7 @@ __global__ __launch_bounds__(256) void env_circ_kernel(EnvArgs a, EnvCirc c)
             const int o = o0 + 4 * kq + r;
             if (o >= c.H) continue;
             const int w = col * c.stride + ph * (c.P == 2 ? c.H4 : 0) + o;
-            const float x = xs[w], y = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+            const float x = xs[w], y = ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) + rest;
             const float e = sqrtf(fmaf(x, x, y * y));
             if (gridDim.y == 1)
                 env[w] = e;

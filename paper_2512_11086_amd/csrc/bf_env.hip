@@ -595,6 +595,16 @@ __device__ inline void fft_dit(float2 *v)
     }
 }
 
+// Between a wavefront's LDS writes and its other lanes' reads of them: keeps
+// the compiler from moving either across (LDS accesses of one wavefront run in
+// order, so no instruction is needed).
+__device__ inline void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Pairs of columns of a wavefront, LDS float2 of a wavefront.
 template <int R, int L> struct EnvTile {
     static constexpr int pairs = 64 / L;
@@ -637,7 +647,7 @@ __global__ __launch_bounds__(256) void env_fft_tile_kernel(EnvArgs a)
         const int k1 = bit_reverse(r, b);
         buf[k1 * (L + 1) + l] = cmul(v[r], tw[k1 * L]);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         float2 w[L];
@@ -659,7 +669,7 @@ __global__ __launch_bounds__(256) void env_fft_tile_kernel(EnvArgs a)
 #pragma unroll
         for (int n2 = 0; n2 < L; ++n2) row[n2] = w[n2];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int k1 = bit_reverse(r, B);

@@ -367,7 +367,7 @@ int Frame::init(const bf_params &src)
 // 3 depths (times the points per lane) by default.  Another shape is taken
 // where it needs clearly less work on this grid, by the vector instructions of
 // a workgroup per trace: 15 per point for the delay, the weight and the address
-// plus 4 per (mirror) point for the read (IQ 35 and 10), about 15 per staged
+// plus 4 per (mirror) point for the read (IQ 36 and 10), about 15 per staged
 // pair of quads, and 250 per wavefront and batch.  The padded points of ragged
 // grids and of mirrored halves decide mostly.  us, default and chosen:
 // 48 x 48 x 96 from 64 x 128 traces 932, 851; 49 x 109 x 120 from 24 x 128 1 290,
@@ -388,7 +388,7 @@ void Frame::choose_box()
             LdsCfg c;
             if (!lds_config(das_args(nullptr, nullptr, p.c), &c)) continue;
             const int nm = mirror_copies(c.mir), waves = bw[0] * bw[1] * bw[2];
-            const double terms = (double)waves * c.zp * (p.iq ? 35 + 10 * nm : 15 + 4 * nm);
+            const double terms = (double)waves * c.zp * (p.iq ? 36 + 10 * nm : 15 + 4 * nm);
             const double staging = 15.0 / 64.0 * nm * c.lmax * (p.iq ? 2 : 1);
             const double cost = (double)c.blocks_x * c.blocks_y * c.blocks_z *
                                 (terms + staging + 250.0 * waves / c.nb);

@@ -136,8 +136,8 @@ struct LaneL {
     float x, y, z, z2, thr, wsc, fB;
     float zk, zk2;  // z / k and its square (k = fs / c): the HERCULES delay
     float wtab;     // 4 u^2 = rho^2 * wtab (q of the Hann table)
-    int nB;
-    float ph0;      // IQ: carrier phase of sample position nB (revolutions)
+    int nB;         // integer sample of the delay (folded IQ reads: less nR)
+    float ph0;      // IQ: carrier phase of that sample (revolutions)
 };
 
 // Grid extents the boxes of a launch cover: the whole grid, or the lower half
@@ -162,8 +162,9 @@ __device__ inline void lane_point(const DasArgs &a, const LdsCfg &c, int bx, int
     *iz = (((bz * c.bwz + wz) << a.lz) + lz) * c.zp + p - c.z_off;
 }
 
-// nref (folded HERCULES reads): fB then holds B - nref in one FP32 rounding.
-template <int MODE, int NM>
+// nref (folded HERCULES reads): fB then holds B - nref in one FP32 rounding; IQ
+// lanes keep the fraction of B there and floor(B) - nref in nB.
+template <int MODE, int NM, bool IQ>
 __device__ inline LaneL lane_setup_l(const DasArgs &a, const LdsCfg &c, int bx, int by, int bz,
                                      int wave, int lane, int p, const int *nref = nullptr)
 {
@@ -190,7 +191,7 @@ __device__ inline LaneL lane_setup_l(const DasArgs &a, const LdsCfg &c, int bx, 
     const double B = (tx_path(a, px, py, pze) + pze) * a.k - a.t0fs;
     const double fl = floor(B);
     L.nB = (int)fl;
-    L.fB = (float)(B - (nref ? (double)*nref : fl));
+    L.fB = (float)(B - (!IQ && nref ? (double)*nref : fl));
     L.z = (float)pze;
     L.z2 = L.z * L.z;
     L.zk = (float)(pze / a.k);
@@ -198,7 +199,9 @@ __device__ inline LaneL lane_setup_l(const DasArgs &a, const LdsCfg &c, int bx, 
     L.thr = (L.valid && pz > 0.0) ? (a.f2 > 0.f ? L.z2 * 0.25f / a.f2 : __builtin_inff()) : -1.f;
     L.wsc = a.f2 > 0.f ? a.f2 / L.z2 : 0.f;
     L.wtab = L.wsc * 4.f;
-    L.ph0 = phase_origin(a, nref ? *nref : L.nB);
+    L.ph0 = phase_origin(a, !IQ && nref ? *nref : L.nB);
+    if constexpr (IQ)
+        if (nref) L.nB -= *nref;
     return L;
 }
 
@@ -850,7 +853,11 @@ __device__ inline float2 hann_entry(unsigned hann, float q)
 // HF (forward reads, cubic or linear): the lanes' fB hold
 // fB + nB - nR for the box's reference sample nR, and neg_w0 carries the
 // LDS byte address of the trace's window less (w0 - nR) intervals, so a read's
-// address is floor(s) * 16 (IQ: 32) plus that value: one shift-add per point.
+// address is floor(s) * 16 plus that value: one shift-add per point.  IQ terms
+// turn s into a phase, where the spread of the box's delays would cost bits of
+// its fraction (boxes of 12 depths 17 samples apart: 4.4e-6 sample RMS against
+// 3.2e-7): their lanes keep fB and nB - nR apart and add the integers, one
+// instruction more of about 50 per term.
 // NM > 1: the point's mirror points take the same delay and weight with the
 // mirror traces, whose windows lie a constant number of sets further
 // (acc[m ZP + p]).
@@ -889,7 +896,10 @@ __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, in
                         s[u] = fmaf(rho2, __builtin_amdgcn_rcpf(dk + l.zk), l.fB);
                         xw[u] = __builtin_amdgcn_fmed3f(rho2 * l.wtab, 0.f, 1.f);
                         h[u] = hann_entry(hann, xw[u]);
-                        ad[u] = ((unsigned)cvt_flr(s[u]) << (QS == 2 ? 5 : 4)) + (unsigned)neg_w0;
+                        if constexpr (QS == 2)
+                            ad[u] = ((unsigned)(cvt_flr(s[u]) + l.nB) << 5) + (unsigned)neg_w0;
+                        else
+                            ad[u] = ((unsigned)cvt_flr(s[u]) << 4) + (unsigned)neg_w0;
                     }
 #pragma unroll
                     for (int m = 0; m < MG; ++m)
@@ -1008,9 +1018,9 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     // sample choice is an integer decision that extra rounding would move at
     // near ties.
     constexpr bool FOLD = SEP && ADJ == 0 && ET != ET_CF32 && IP != IN_NEAREST;
-    // HERCULES forward reads fold the lane's integer sample nB,
-    // less a box reference nR, into its FP32 position (hercules_term, HF);
-    // nearest reads keep the unsplit position, as above
+    // HERCULES forward reads fold the lane's integer sample nB, less a box
+    // reference nR, into its FP32 position (IQ: into the address, see
+    // hercules_term, HF); nearest reads keep the unsplit position, as above
     constexpr bool HF = MODE == MODE_HERCULES && ADJ == 0 && IP != IN_NEAREST;
     static_assert(NM == 1 || HF, "mirror points: HERCULES forward, cubic or linear");
     const int hc = FOLD ? c.lmax >> 2 : 0;
@@ -1067,7 +1077,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     const int nR = HF ? (int)floorf(fmaf(box.txlo + fmaxf(box.zmax, 0.f), box.kf, -box.t0f)) : 0;
     LaneL Lp[ZP];
 #pragma unroll
-    for (int p = 0; p < ZP; ++p) Lp[p] = lane_setup_l<MODE, NM>(a, c, bx, by, bz, wave, lane, p, HF ? &nR : nullptr);
+    for (int p = 0; p < ZP; ++p) Lp[p] = lane_setup_l<MODE, NM, ET == ET_CF32>(a, c, bx, by, bz, wave, lane, p, HF ? &nR : nullptr);
     const LaneL &L = Lp[0];
     // largest rho^2 bound of the receive aperture over the lane's points
     float thr_l = Lp[0].thr;

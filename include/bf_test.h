@@ -31,6 +31,15 @@ int bf_test_set_stack_cap(bf_plan plan, int32_t cap);
  * compare mirrored launches with plain ones. */
 int bf_test_set_mirrors(bf_plan plan, int32_t allowed);
 
+/* The launch bf_das would make for a description, on the host alone (no device
+ * is needed), with the mirror axes restricted to `allowed`: lds = 0 is the
+ * gather kernel; nb counts the traces per batch and mirror copy, mirrors the
+ * axes used, blocks the workgroup boxes along x, y and z. */
+typedef struct {
+    int32_t lds, mirrors, nb, zp, tile[3], block[3], blocks[3], lmax, groups, adj_groups;
+} bf_test_launch;
+int bf_test_das_launch(const bf_params *params, int32_t allowed, bf_test_launch *out);
+
 #ifdef __cplusplus
 }
 #endif

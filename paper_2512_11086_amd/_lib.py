@@ -74,6 +74,13 @@ class BatchFrameInfo(ctypes.Structure):
                 ("das_items", ctypes.c_int64)]
 
 
+class TestLaunch(ctypes.Structure):
+    _fields_ = [("lds", ctypes.c_int32), ("mirrors", ctypes.c_int32), ("nb", ctypes.c_int32),
+                ("zp", ctypes.c_int32), ("tile", ctypes.c_int32 * 3), ("block", ctypes.c_int32 * 3),
+                ("blocks", ctypes.c_int32 * 3), ("lmax", ctypes.c_int32), ("groups", ctypes.c_int32),
+                ("adj_groups", ctypes.c_int32)]
+
+
 BATCH_PATHS = {0: "persistent_lds", 1: "gather", 2: "frame_lds"}
 
 _lib = None
@@ -114,6 +121,7 @@ def lib():
         "bf_test_hann_poly": ([dbl], dbl),
         "bf_test_set_stack_cap": ([vp, i32], ctypes.c_int),
         "bf_test_set_mirrors": ([vp, i32], ctypes.c_int),
+        "bf_test_das_launch": ([P(Params), i32, P(TestLaunch)], ctypes.c_int),
         "bf_demod_create": ([P(DemodParams), P(vp)], ctypes.c_int),
         "bf_demod_destroy": ([vp], ctypes.c_int),
         "bf_demod_out_samples": ([vp, P(i32)], ctypes.c_int),
@@ -146,6 +154,7 @@ EXPORTED = ("bf_abi_version", "bf_last_error", "bf_validate", "bf_plan_create",
             "bf_batch_run", "bf_graph_launch", "bf_batch_get_frame_info", "bf_demod_create",
             "bf_demod_destroy", "bf_demod_out_samples", "bf_demodulate", "bf_env_create",
             "bf_env_destroy", "bf_envelope")
-TEST_HOOKS = ("bf_test_hann_poly", "bf_test_set_stack_cap", "bf_test_set_mirrors")   # include/bf_test.h
+TEST_HOOKS = ("bf_test_hann_poly", "bf_test_set_stack_cap", "bf_test_set_mirrors",   # include/bf_test.h
+              "bf_test_das_launch")
 COMPRESS = {"none": 0, "log": 1, "power": 2}
 VARIANTS = {"lds": 0, "gather": 1, "lds2": 2}   # BF_DAS_LDS, BF_DAS_GATHER, BF_DAS_LDS_Z2

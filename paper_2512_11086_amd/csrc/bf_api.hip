@@ -170,8 +170,9 @@ Frame::~Frame()
     for (void *p : allocs) (void)hipFree(p);
 }
 
-// Build host tables and upload them for one frame.
-int Frame::init(const bf_params &src)
+// Description, geometry and launch configuration of one frame: host work only.
+// allowed: mirror axes that the plan may use (bit 0: y, bit 1: x).
+void Frame::configure(const bf_params &src, int allowed)
 {
     p = src;
     const int n = p.n_tx;
@@ -181,7 +182,6 @@ int Frame::init(const bf_params &src)
         H.assign((size_t)n * n, 0);
         for (int i = 0; i < n; ++i) H[(size_t)i * n + i] = 1;
     }
-    std::vector<float2> tx_sc;
     if (p.mode == BF_TPW_3D)
         for (int i = 0; i < n; ++i) {
             const double th = p.tx_angles[i], sh = sin(0.5 * th);
@@ -198,21 +198,12 @@ int Frame::init(const bf_params &src)
     p.channel_map = nullptr;
 
     kb = (n + 31) / 32;
-    const int KP = 32 * kb;
-    std::vector<int8_t> At((size_t)KP * KP, 0);
-    std::vector<int> cs(KP, 0);
-    std::vector<float> Hf((size_t)n * KP, 0.f);
-    for (int k = 0; k < n; ++k)
-        for (int m = 0; m < n; ++m) {
-            At[(size_t)m * KP + k] = H[(size_t)k * n + m];
-            cs[m] += H[(size_t)k * n + m];
-            Hf[(size_t)k * KP + m] = (float)H[(size_t)k * n + m];
-        }
 
     // Lateral reference: centre of the element grid (keeps FP32 offsets small).
     const double cx = 0.5 * (p.n_elem[0] - 1) * p.pitch[0];
     const double cy = 0.5 * (p.n_elem[1] - 1) * p.pitch[1];
-    std::vector<float> tx_x(n), rx_c(p.n_ch);
+    tx_x.resize(n);
+    rx_c.resize(p.n_ch);
     for (int i = 0; i < n; ++i) tx_x[i] = (float)(tx[i] * p.pitch[0] - cx);
     for (int j = 0; j < p.n_ch; ++j)
         rx_c[j] = (float)(p.mode == BF_FORCES_2D ? ch[j] * p.pitch[0] - cx : ch[j] * p.pitch[1] - cy);
@@ -279,6 +270,7 @@ int Frame::init(const bf_params &src)
         }
     }
     find_mirrors();
+    mirrors &= allowed;
     sorted_tx = 1;
     for (int i = 1; i < n; ++i)
         if (tx_x[i] < tx_x[i - 1]) sorted_tx = 0;
@@ -293,6 +285,25 @@ int Frame::init(const bf_params &src)
         tx_x0 = tx_x[0];
         tx_inv_dx = (float)(1.0 / (step * p.pitch[0]));
     }
+    choose_box();
+    choose_groups();
+}
+
+// Configure one frame, build its device tables and upload them.
+int Frame::init(const bf_params &src)
+{
+    configure(src);
+    const int n = p.n_tx;
+    const int KP = 32 * kb;
+    std::vector<int8_t> At((size_t)KP * KP, 0);
+    std::vector<int> cs(KP, 0);
+    std::vector<float> Hf((size_t)n * KP, 0.f);
+    for (int k = 0; k < n; ++k)
+        for (int m = 0; m < n; ++m) {
+            At[(size_t)m * KP + k] = H[(size_t)k * n + m];
+            cs[m] += H[(size_t)k * n + m];
+            Hf[(size_t)k * KP + m] = (float)H[(size_t)k * n + m];
+        }
 
     d_At = (int8_t *)alloc(At.size());
     d_colsum = (int *)alloc(cs.size() * sizeof(int));
@@ -341,8 +352,6 @@ int Frame::init(const bf_params &src)
         hipError_t he = hipMemcpy(d_hann, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
         if (he != hipSuccess) return hip_fail(he, "upload of the Hann table");
     }
-    choose_box();
-    choose_groups();
     if (groups > 1) {
         d_part = (float *)alloc((size_t)groups * out_elems() * sizeof(float));
         if (!d_part) return fail(BF_ERR_HIP, "device allocation of partial images failed");
@@ -598,8 +607,10 @@ static size_t lds_cap_bytes(size_t most = 80 * 1024)
         int dev = 0, v = 0;
         (void)hipGetDevice(&dev);
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
-            v <= 0)
-            v = 64 * 1024;
+            v <= 0) {
+            (void)hipGetLastError();
+            v = 160 * 1024;      // (no device: gfx950's)
+        }
         return (size_t)v;
     }();
     return std::min(device, most);
@@ -1221,6 +1232,37 @@ int bf_test_set_mirrors(bf_plan plan, int32_t allowed)
             used |= cfg.mir;
     }
     return used;
+}
+
+int bf_test_das_launch(const bf_params *params, int32_t allowed, bf_test_launch *out)
+{
+    g_err.clear();
+    if (!out) return fail(BF_ERR_NULL, "out is NULL");
+    const int st = validate_params(params);
+    if (st != BF_OK) return st;
+    Frame f;
+    f.configure(*params, allowed);
+    memset(out, 0, sizeof *out);
+    out->groups = f.groups;
+    out->adj_groups = f.adj_groups;
+    LdsCfg c;
+    if (f.variant == BF_DAS_GATHER || !f.lds_config(f.das_args(nullptr, nullptr, f.p.c), &c, 0, nullptr, true))
+        return BF_OK;
+    out->lds = 1;
+    out->mirrors = c.mir;
+    out->nb = c.nb;
+    out->zp = c.zp;
+    out->tile[0] = 1 << f.lx;
+    out->tile[1] = 1 << f.ly;
+    out->tile[2] = 1 << f.lz;
+    out->block[0] = c.bwx;
+    out->block[1] = c.bwy;
+    out->block[2] = c.bwz;
+    out->blocks[0] = c.blocks_x;
+    out->blocks[1] = c.blocks_y;
+    out->blocks[2] = c.blocks_z;
+    out->lmax = c.lmax;
+    return BF_OK;
 }
 
 int bf_test_set_stack_cap(bf_plan plan, int32_t cap)

@@ -21,6 +21,8 @@ struct Frame {
     bf_params p;                 // copy; pointer members cleared
     std::vector<int8_t> H;       // [n_tx][n_tx]
     std::vector<int> tx, ch;     // element column / channel element
+    std::vector<float> tx_x, rx_c;   // their positions from the array centre
+    std::vector<float2> tx_sc;   // TPW: (sin, cos - 1) per transmit
     int kb = 1;                  // 32-wide K blocks of the int8 decode
     Grid grid;
     int lx = 2, ly = 2, lz = 2;  // DAS wavefront tile (log2)
@@ -50,6 +52,7 @@ struct Frame {
 
     ~Frame();
     void *alloc(size_t bytes);
+    void configure(const bf_params &src, int allowed = 3);
     int init(const bf_params &src);
     void set_tile(int lx, int ly, int lz);
     void find_mirrors();

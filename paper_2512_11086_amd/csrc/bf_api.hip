@@ -374,11 +374,9 @@ int Frame::init(const bf_params &src)
 
 // Lane tile and workgroup shape of a HERCULES plan: 12 wavefronts as 16 x 16 x
 // 3 depths (times the points per lane) by default.  Another shape is taken
-// where it needs clearly less work on this grid, by the vector instructions of
-// a workgroup per trace: 15 per point for the delay, the weight and the address
-// plus 4 per (mirror) point for the read (IQ 36 and 10), about 15 per staged
-// pair of quads, and 250 per wavefront and batch.  The padded points of ragged
-// grids and of mirrored halves decide mostly.  us, default and chosen:
+// where it needs clearly less work on this grid (launch_cost, with the mirror
+// axes that suit it).  The padded points of ragged grids and of mirrored halves
+// decide mostly.  us, default and chosen:
 // 48 x 48 x 96 from 64 x 128 traces 932, 851; 49 x 109 x 120 from 24 x 128 1 290,
 // 1 160; IQ 32 x 24 x 144 from 20 x 116 376, 300; IQ 118 x 128 x 71 from 20 x 64
 // 969, 846.  The count is good to about 5 %, so a shape has to be 6 % better.
@@ -396,11 +394,7 @@ void Frame::choose_box()
             for (int r = 0; r < 3; ++r) bw[r] = blocks[b][r];
             LdsCfg c;
             if (!lds_config(das_args(nullptr, nullptr, p.c), &c)) continue;
-            const int nm = mirror_copies(c.mir), waves = bw[0] * bw[1] * bw[2];
-            const double terms = (double)waves * c.zp * (p.iq ? 36 + 10 * nm : 15 + 4 * nm);
-            const double staging = 15.0 / 64.0 * nm * c.lmax * (p.iq ? 2 : 1);
-            const double cost = (double)c.blocks_x * c.blocks_y * c.blocks_z *
-                                (terms + staging + 250.0 * waves / c.nb);
+            const double cost = launch_cost(c);
             if (t == 0 && b == 0) first = cost;
             if (cost < best) {
                 best = cost;
@@ -620,32 +614,60 @@ static size_t lds_cap_bytes(size_t most = 80 * 1024)
 // The wavefront tile is a's; bw_adj (if set) replaces the plan's workgroup
 // shape.
 // solo: a launch of its own (bf_das), whose workgroups may take a whole CU each.
+//
+// Mirror points: a mirrored axis needs the boxes of its lower half only, each
+// with twice the points.  Of the plain launch and those over the plan's mirror
+// axes that fit LDS, the one with the fewest boxes is taken, a box counting 1
+// plain, 1.45 mirrored along one axis and 2.4 along both (an axis of few boxes
+// halves badly), unless launch_cost, which knows the windows and the batch,
+// finds another 30 % cheaper (long windows leave a mirrored batch few
+// traces).  Over 240 symmetric geometries in 16 x 16 x 3 boxes (24 to 128 points
+// a side, 8 to 256 transmits, windows of 16 to 300 quads) the choice is on
+// average 2.1 % slower than the fastest timed; by boxes alone 2.7 %, by
+// launch_cost alone 4.3 %.  A launch that does not fit with mirror points may
+// still fit plain.
+// Nearest reads keep the unsplit position, which the mirror terms do not have.
 bool Frame::lds_config(const DasArgs &a, LdsCfg *cfg, int adj, const int *bw_adj, bool solo) const
+{
+    if (adj || p.interp == BF_INTERP_NEAREST) return fit_config(a, MIRROR_NONE, cfg, adj, bw_adj, solo);
+    const double weight[4] = {1.0, 1.45, 1.45, 2.4};
+    LdsCfg c[4];
+    int few = -1, cheap = -1;
+    double boxes[4], cost[4];
+    for (int m = MIRROR_NONE; m <= MIRROR_XY; ++m) {
+        if ((mirrors & m) != m || !fit_config(a, m, &c[m], adj, bw_adj, solo)) continue;
+        boxes[m] = weight[m] * c[m].blocks_x * c[m].blocks_y;
+        cost[m] = launch_cost(c[m]);
+        if (few < 0 || boxes[m] < boxes[few]) few = m;
+        if (cheap < 0 || cost[m] < cost[cheap]) cheap = m;
+    }
+    if (few < 0) return false;
+    *cfg = c[cost[cheap] < 0.7 * cost[few] ? cheap : few];
+    return true;
+}
+
+// Vector instructions of a HERCULES launch per trace: 15 per wavefront and
+// point for the delay, the weight and the address plus 4 per (mirror) point for
+// the read (IQ 35 and 10), about 15 per staged pair of quads, and 250 per
+// wavefront and batch.
+double Frame::launch_cost(const LdsCfg &c) const
+{
+    const int nm = mirror_copies(c.mir), waves = c.bwx * c.bwy * c.bwz;
+    const double terms = (double)waves * c.zp * (p.iq ? 35 + 10 * nm : 15 + 4 * nm);
+    const double staging = 15.0 / 64.0 * nm * c.lmax * (p.iq ? 2 : 1);
+    return (double)c.blocks_x * c.blocks_y * c.blocks_z * (terms + staging + 250.0 * waves / c.nb);
+}
+
+// lds_config over the mirror axes mir (forward reads only).
+bool Frame::fit_config(const DasArgs &a, int mir, LdsCfg *cfg, int adj, const int *bw_adj, bool solo) const
 {
     const bool sep = p.mode != BF_HERCULES_3D;   // separable: FORCES, TPW, VLS
     const int *bw = bw_adj ? bw_adj : this->bw;
     const int lx = a.lx, ly = a.ly, lz = a.lz;
     const int tx = bw[0] << lx, ty = bw[1] << ly;
-    // Mirror points: a mirrored axis needs the boxes of its lower half only,
-    // each with twice the points.  The axes are taken that make the launch
-    // cheapest, counting a box as 1 plain, 1.45 mirrored along one axis and
-    // 2.4 along both (headline volume, us: 22 830 plain, 16 480 mirrored in y,
-    // 13 720 in x and y; its IQ counterpart with 64 x 64 traces 1 668, 1 132
-    // and 1 022): an axis of few boxes halves badly.  Nearest reads keep
-    // the unsplit position, which the mirror terms do not have.
-    cfg->mir = MIRROR_NONE;
-    cfg->ex = grid.nx;
-    cfg->ey = grid.ny;
-    if (!sep && adj == 0 && p.interp != BF_INTERP_NEAREST) {
-        auto boxes = [](int n, int t) { return (n + t - 1) / t; };
-        const double bx = boxes(grid.nx, tx), by = boxes(grid.ny, ty);
-        const double hx = boxes((grid.nx + 1) / 2, tx), hy = boxes((grid.ny + 1) / 2, ty);
-        const double cost[4] = {bx * by, 1.45 * bx * hy, 1.45 * hx * by, 2.4 * hx * hy};
-        for (int m = 1; m < 4; ++m)
-            if ((mirrors & m) == m && cost[m] < cost[cfg->mir]) cfg->mir = m;
-        if (cfg->mir & MIRROR_Y) cfg->ey = (grid.ny + 1) / 2;
-        if (cfg->mir & MIRROR_X) cfg->ex = (grid.nx + 1) / 2;
-    }
+    cfg->mir = mir;
+    cfg->ex = mir & MIRROR_X ? (grid.nx + 1) / 2 : grid.nx;
+    cfg->ey = mir & MIRROR_Y ? (grid.ny + 1) / 2 : grid.ny;
     const int nm = mirror_copies(cfg->mir);
     // points per lane along z: two for the real-data variant without mirror
     // points (with them one: 13 720 against 14 620 us in x and y, and boxes

@@ -153,7 +153,8 @@ __host__ __device__ constexpr int mirror_copies(int mir)
 // Quads of one window set of a mirrored launch: copy m of a batch's windows
 // starts m sets after copy 0, a constant that the reads carry as their
 // immediate offset.  Two batches of NM sets fill what the 80 KiB of a
-// workgroup leave beside the tables (at n_tx, n_ch <= 256).
+// workgroup leave beside the tables and the guard of usual grids (n_tx, n_ch <=
+// 256); with larger tables or a longer guard fewer copies, or none, are used.
 __host__ __device__ constexpr int mirror_set_quads(int nm) { return nm == 4 ? 484 : 968; }
 
 // Workgroups of a single-frame LDS launch (box order xcd_slab_box): whole

@@ -66,6 +66,8 @@ struct Frame {
     DasArgs das_args(const void *e, float *out, double c) const;
     bool lds_config(const DasArgs &a, LdsCfg *cfg, int adj = 0, const int *bw_adj = nullptr,
                     bool solo = false) const;
+    bool fit_config(const DasArgs &a, int mir, LdsCfg *cfg, int adj, const int *bw_adj, bool solo) const;
+    double launch_cost(const LdsCfg &c) const;
     void adjoint_e_tile(DasArgs *a, int bw_out[3]) const;   // the RF gradient's lane tile
     bool z2_ok() const;          // two depth points per lane apply to this frame
     int decode(const int16_t *rf, void *e, hipStream_t s) const;

@@ -75,3 +75,24 @@ def test_headline_volume_mirrors_both_axes():
     assert got.lds and got.mirrors == 3 and (got.nb, got.zp) == (15, 1)
     assert math.prod(got.block) == 12 and tuple(got.tile) == (8, 8, 1)
 
+
+def test_real_data_boxes_keep_the_bits_of_a_position():
+    """FP32 positions relative to the middle of a box's delays lose bits as these
+    spread: boxes deeper than the default's 6 depths stay within 16 samples."""
+    rng = random.Random(3)
+    shapes, deeper = set(), 0
+    for _ in range(600):
+        n = rng.choice([32, 64, 128])
+        half = rng.uniform(0.3, 1) * n * 0.1e-3
+        d = _desc(n, n, 0.2e-3, rng.choice([20e6, 30e6]),
+                  (rng.randint(16, 128), rng.randint(16, 128), rng.randint(4, 256)), (half, half),
+                  (5e-3, rng.uniform(15e-3, 45e-3)))
+        if rng.random() < 0.5:
+            d["channel_map"] = np.roll(np.arange(n), 1)       # no mirror in y
+        got = _launch(d, rng.choice([0, 3]))
+        depths = got.tile[2] * got.block[2] * got.zp
+        step = 2 * d["fs"] / d["c"] * (d["gmax"][2] - d["gmin"][2]) / (d["dims"][2] - 1)
+        assert depths <= 6 or step * (depths - 1) / 2 <= 16, d
+        deeper += depths > 6
+        shapes.add((tuple(got.tile), tuple(got.block)))
+    assert len(shapes) > 2 and deeper

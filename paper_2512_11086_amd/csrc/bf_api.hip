@@ -765,17 +765,27 @@ bool Frame::fit_config(const DasArgs &a, int mir, LdsCfg *cfg, int adj, const in
         nbb -= unit;
     if (nbb < unit || nthr > 1024) return false;
     // A launch with at most one workgroup per CU (a small plane, a row-column
-    // volume of few points) fills larger batches: each batch costs the latency
-    // of its loads and a barrier, which nothing else on the CU covers (128 x 128
-    // points from 32 x 32 traces: 36 us with batches of 8 traces, 32 with 16).
+    // volume of few points) may fill a CU's LDS with its batches: each batch costs
+    // the latency of its loads and a barrier, which nothing else on the CU covers
+    // (128 x 128 points from 32 x 32 traces: 36 us with batches of 8 traces, 32
+    // with 16).  The workgroups per CU are those of the XCD with most depth slabs:
+    // where it has more than its 32 CUs, a second round would wait for the first
+    // (252 x 106 points from 24 x 36 traces, 36 workgroups on 7 XCDs: 43 us with
+    // batches of 12, 50 with 16).  Batches grow only to save one per row chunk
+    // (TPW, 2 x 2 x 28 boxes from 24 transmits: 3 batches of 8 transmits 140 us,
+    // 10, 10 and 4 148).
     // (which kernel runs is decided by the shared cap alone)
-    const long wgs = (long)((cfg->ex + tx - 1) / tx) * ((cfg->ey + ty - 1) / ty) *
-                     ((grid.nz + z_off + tz - 1) / tz) * a.groups;
-    if (solo && sep && adj == 0 && wgs <= 256) {
+    const long slabs = (grid.nz + z_off + tz - 1) / tz;
+    const long per_xcd = (long)((cfg->ex + tx - 1) / tx) * ((cfg->ey + ty - 1) / ty) *
+                         ((slabs + 7) / 8) * a.groups;
+    if (solo && sep && adj == 0 && per_xcd <= 32) {
         const size_t whole = lds_cap_bytes(152 * 1024);
-        while (nbb + unit <= nb && rounds(nbb + unit) <= max_rounds &&
-               lds_bytes(p.n_tx, p.n_ch, nbb + unit, lmax, qs, guard, adj, p.mode, nm) <= whole)
-            nbb += unit;
+        auto batches = [&](int n) { return (p.n_tx + n / unit - 1) / (n / unit); };
+        int most = nbb;
+        while (most + unit <= nb && rounds(most + unit) <= max_rounds &&
+               lds_bytes(p.n_tx, p.n_ch, most + unit, lmax, qs, guard, adj, p.mode, nm) <= whole)
+            most += unit;
+        while (batches(nbb) > batches(most)) nbb += unit;
     }
     cfg->bwx = bw[0];
     cfg->bwy = bw[1];

@@ -428,30 +428,39 @@ void Frame::choose_box()
 // added in a fixed order afterwards.
 //
 // adj_groups, the adjoint's split and the floor of the forward one, gives at
-// least 8192 wavefronts.  The forward split counts workgroups of the plan's
-// LDS launch, two per CU (512 slots):
-//  - Planes stage channels in chunks of JC rows, so a group of m chunks costs
-//    about m plus 1/4 for its setup; the m is taken whose rounds over the
-//    slots cost least (a round that is not full is partly hidden by the
-//    shallow boxes, which have fewer active rows).  256 x 256 points, 64
-//    traces (64 boxes): m = 1, 2, 4 run 131, 123, 155 us; 181 x 303 points,
-//    127 rows (57 boxes): 132, 127, 145 us, and 149 with the 10 groups of the
-//    floor.
-//    Planes of FP32 data keep the floor: they are the autofocus' planes, whose
-//    dL/dc is the small rest of a sum that cancels and shows every change of
-//    the image's rounding.
-//  - TPW and VLS volumes weigh whole chunks likewise: a group costs its m
-//    chunks and a setup that shrinks with the transmits, a launch its
-//    workgroups per slot and 0.4 for the last, partly filled one; a split has
-//    to be 5 % better by this count than none.  VLS 44 x 34 x 195 points from
-//    44 x 64 traces (594 boxes), G = 1, 2, 3, 4, 8: 570, 539, 564, 501, 511 us;
-//    TPW 37 x 27 x 147 from 32 x 64 (294 boxes), 1, 2, 4, 5, 8: 258, 238, 199,
-//    232, 205; 102 x 76 x 121 from 24 x 32 (1435 boxes), 1, 2: 285, 291.
+// least 8192 wavefronts.  The forward split counts rounds: a launch's boxes go to
+// the 8 XCDs by depth slab (xcd_slab_box), so the XCD with most slabs sets the
+// time, and its 32 CUs hold two workgroups each.  A round that is not full is
+// partly hidden by the shallow boxes, which have fewer active rows, but one
+// workgroup too many costs: 31 x 31 x 77 points from 16 x 116 traces, 8 boxes per
+// XCD, 152 us with 8 groups, 173 with 9.
+//  - Planes stage channels in chunks of JC rows: a group of m chunks costs m and
+//    a setup that weighs more with few transmits.  Of the floor and the
+//    whole-chunk splits the one is taken whose rounds cost least (a split by 3 %
+//    less than the floor).  Over 89 IQ and 86 BF16 or INT32 planes (8 to 128
+//    transmits, 16 to 128 channels, 100 to 400 x 100 to 512 points) it is on
+//    average 20 and 18 % faster than the floor and 1.3 and 1.0 % slower than the
+//    best split timed; one is slower than the floor (25 channels, 12 %).
+//    FP32 planes keep the floor (the same rule would make 45 of them 22 %
+//    faster): their images feed the autofocus' dL/dc, the small rest of a sum
+//    that cancels, which another order of the channel sum moves by more than
+//    its own last bit.
+//  - TPW and VLS volumes weigh whole chunks: a group costs its m chunks and a
+//    setup that shrinks with the transmits, a launch its workgroups per slot and
+//    0.4 for the last, partly filled one; a split has to be 5 % better by this
+//    count than none.  VLS 44 x 34 x 195 points from 44 x 64 traces (594 boxes),
+//    G = 1, 2, 3, 4, 8: 570, 539, 564, 501, 511 us; TPW 37 x 27 x 147 from 32 x 64
+//    (294 boxes), 1, 2, 4, 5, 8: 258, 238, 199, 232, 205; 102 x 76 x 121 from
+//    24 x 32 (1435 boxes), 1, 2: 285, 291.  Another whole-chunk split, or the
+//    floor, is taken where its rounds are 12 % cheaper: over 130 volumes 1.2 %
+//    slower than the best split timed, 2.2 without this, 8.5 with the floor.
 //  - HERCULES volumes aim at five workgroups per slot: 61 x 53 x 97 points from
 //    24 x 100 traces 764 us with 2 groups, 627 with 10; IQ 64 x 64 x 128 from 64
 //    x 64 traces 2 090 us with 1, 1 020 with 8.  A group keeps at least 192
 //    traces and two rows: below that the partial images cost more than the
-//    balance gains.
+//    balance gains.  Another split, down to 96 traces, is taken where its rounds
+//    are 20 % cheaper: over 150 volumes 2.4 % slower than the best split timed,
+//    4.0 without this, 13.4 with the floor.
 // The partial images stay within BF_DAS_NOALLOC_MAX_BYTES.
 void Frame::choose_groups()
 {
@@ -462,28 +471,33 @@ void Frame::choose_groups()
     groups = adj_groups;
     LdsCfg c;
     if (variant == BF_DAS_GATHER || !lds_config(das_args(nullptr, nullptr, p.c), &c)) return;
+    if (p.mode == BF_FORCES_2D && p.e_type == BF_E_F32 && !p.iq) return;
     const long boxes = (long)c.blocks_x * c.blocks_y * c.blocks_z;
     const long slots = 512;
     const long cap = std::max<long>(1, BF_DAS_NOALLOC_MAX_BYTES / (out_elems() * (long)sizeof(float)));
-    long G = 1;
     const int chunks = (p.n_ch + JC - 1) / JC;
+    auto chunks_of = [&](long g) { return (double)((chunks + g - 1) / g); };
+    // rounds of the fullest XCD with g groups: the last, partial one costs `last`
+    // more than its share, or all of it but `hidden`
+    const double per_xcd = (double)(xcd_slab_grid(c) / 8) / (slots / 8);
+    auto rounds = [&](long g, double last, double hidden) {
+        const double r = per_xcd * g;
+        return r <= 0.5 ? 0.7 : r <= 1.0 ? 1.0 : std::max(r + last, ceil(r) - hidden);
+    };
     if (p.mode == BF_FORCES_2D) {
-        if (p.e_type == BF_E_F32 && !p.iq) return;
-        double best = 1e300;
-        for (int m = 1; m <= chunks; ++m) {
+        auto cost = [&](long g) { return rounds(g, 0.2, 0.45) * (chunks_of(g) + 5.0 / p.n_tx); };
+        double best = 0.97 * cost(adj_groups);
+        for (int m = chunks; m >= 1; --m) {
             const long g = (chunks + m - 1) / m;
-            if (g > cap || g > gmax) continue;
-            const double r = (double)(boxes * g) / slots;
-            const double rounds = r <= 0.5 ? 0.7 : r <= 1.0 ? 1.0 : std::max(r, ceil(r) - 0.3);
-            if (rounds * (m + 0.25) < best) {
-                best = rounds * (m + 0.25);
-                G = g;
-            }
+            if (g > cap || cost(g) >= best) continue;
+            best = cost(g);
+            groups = (int)g;
         }
-        groups = (int)G;
         return;
     }
-    if (p.mode != BF_HERCULES_3D) {
+    const bool hercules = p.mode == BF_HERCULES_3D;
+    long G = 1;
+    if (!hercules) {
         const double setup = 0.1 + 8.0 / p.n_tx;
         double best = 0.95 * ((double)boxes / slots + 0.4) * (chunks + setup);
         for (int m = 2; m < chunks; ++m) {
@@ -495,13 +509,27 @@ void Frame::choose_groups()
                 G = g;
             }
         }
-        groups = (int)G;
-        return;
+    } else {
+        G = (5 * slots + boxes - 1) / boxes;
+        G = std::min(G, (long)p.n_tx * p.n_ch / 192);
+        G = std::min(G, (long)p.n_ch / 2);
+        G = std::max<long>(adj_groups, std::min<long>(std::min<long>(G, 16), cap));
     }
-    G = (5 * slots + boxes - 1) / boxes;
-    G = std::min(G, (long)p.n_tx * p.n_ch / 192);
-    G = std::min(G, (long)p.n_ch / 2);
-    groups = (int)std::max<long>(adj_groups, std::min<long>(std::min<long>(G, 16), cap));
+    groups = (int)G;
+    auto cost = [&](long g) {
+        return hercules ? rounds(g, 0.0, 0.0) / g : rounds(g, 0.3, 0.15) * (chunks_of(g) + 8.0 / p.n_tx);
+    };
+    double best = (hercules ? 0.8 : 0.88) * cost(G);
+    const long low = hercules ? adj_groups : 1;
+    const long high = hercules ? std::min((long)p.n_tx * p.n_ch / 96, (long)p.n_ch / 2) : chunks;
+    for (long g = low; g <= std::min<long>(std::min<long>(high, 16), cap); ++g) {
+        const long m = (long)chunks_of(g);
+        if (!hercules && g != adj_groups && (chunks + m - 1) / m != g) continue;   // (whole chunks)
+        if (cost(g) < best) {
+            best = cost(g);
+            groups = (int)g;
+        }
+    }
 }
 
 // Axes along which a HERCULES geometry is its own mirror image about the

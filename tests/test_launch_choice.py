@@ -67,3 +67,29 @@ def test_a_larger_batch_saves_one():
     assert (list(o.blocks), o.groups, _per_xcd(o), o.nb) == ([4, 1, 7], 9, 36, 12)
     o = _launch("forces", 32, 0.2 * MM, 20e6, 32, 32, (128, 1, 128), 6.4 * MM, (5 * MM, 40 * MM))
     assert (_per_xcd(o), o.nb) == (16, 16)
+
+
+# Splits that the whole launch's workgroups, rounded-down channel counts or a
+# loop that began at two chunks had made too fine or too coarse: (description,
+# smallest and largest number of groups that suits the XCDs' rounds).
+CASES = [
+    # 8 boxes per XCD: 8 groups are one round, 9 the start of another (152, 173 us)
+    (("hercules", 128, 0.1 * MM, 30e6, 16, 116, (31, 31, 77), 6.4 * MM, (5 * MM, 30 * MM)), {}, 8, 8),
+    # 16 groups 123 us, 11 (one workgroup more than a round) 132
+    (("forces", 128, 0.1 * MM, 15e6, 12, 128, (113, 1, 272), 6.39 * MM, (4.6 * MM, 30 * MM)),
+     dict(iq=True, interp="linear"), 16, 16),
+    (("forces", 64, 0.2 * MM, 15e6, 24, 34, (257, 1, 335), 6.0 * MM, (5 * MM, 30 * MM)),
+     dict(iq=True), 7, 9),
+    # 11 chunks of 4 rows: one group per chunk is allowed
+    (("forces", 64, 0.2 * MM, 15e6, 32, 42, (60, 1, 60), 6.0 * MM, (5 * MM, 14 * MM)),
+     dict(iq=True), 11, 11),
+    # half a workgroup per CU, or less, with one chunk a group
+    (("tpw", 32, 0.2 * MM, 20e6, 16, 16, (24, 24, 48), 3.2 * MM, (4 * MM, 40 * MM)), {}, 4, 4),
+    (("tpw", 32, 0.2 * MM, 20e6, 16, 8, (24, 24, 48), 3.2 * MM, (4 * MM, 40 * MM)), {}, 2, 2),
+]
+
+
+@pytest.mark.parametrize("args, kw, low, high", CASES)
+def test_groups_follow_the_rounds_of_the_fullest_xcd(args, kw, low, high):
+    o = _launch(*args, **kw)
+    assert o.lds and low <= o.groups <= high

@@ -245,16 +245,14 @@ int bf_das(bf_plan plan, const void *e, float *out, double c, void *stream);
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and the same result bit for bit, but the partial images of a
  * channel-split launch (grids with few workgroups; see
- * bf_plan_info.channel_groups) go to a static device array of
- * BF_DAS_NOALLOC_MAX_BYTES per GPU, which the library holds until the process
- * ends, instead of plan memory.  The call itself allocates nothing (the plan
- * is created beforehand, with its tables).  Every call on a GPU shares that
- * GPU's array, so calls that overlap on one GPU (other streams, other host
- * threads) race; calls queued on one stream do not.  The current device must
- * be the plan's (BF_ERR_STATE otherwise).  BF_ERR_TOO_LARGE if the plan's
- * partial images exceed the array (the channel split keeps them within 32 MiB
- * for every plan).  Other errors as bf_das. */
-#define BF_DAS_NOALLOC_MAX_BYTES (32u << 20)
+ * bf_plan_info.channel_groups) of up to BF_DAS_NOALLOC_MAX_BYTES go to a static
+ * device array of that size per GPU, which the library holds until the process
+ * ends, instead of plan memory; larger ones (at most 32 MiB) to the plan's own.
+ * The call itself allocates nothing (the plan is created beforehand, with its
+ * tables).  Every call on a GPU shares that GPU's array, so calls that overlap
+ * on one GPU (other streams, other host threads) race; calls queued on one
+ * stream do not.  The current device must be the plan's (BF_ERR_STATE otherwise).  Other errors as bf_das. */
+#define BF_DAS_NOALLOC_MAX_BYTES (8u << 20)
 int bf_das_noalloc(bf_plan plan, const void *e, float *out, double c, void *stream);
 
 /* Decode fused into DAS (Sec. VII-C's decode -> beamform order in one

@@ -289,8 +289,20 @@ void Frame::configure(const bf_params &src, int allowed)
     choose_groups();
 }
 
-// Configure one frame, build its device tables and upload them.
-int Frame::init(const bf_params &src)
+// Partial images of the frame's own channel-split launches (once; a frame of a
+// batch that runs in a persistent launch needs none).
+int Frame::alloc_part()
+{
+    if (groups > 1 && !d_part) {
+        d_part = (float *)alloc((size_t)groups * out_elems() * sizeof(float));
+        if (!d_part) return fail(BF_ERR_HIP, "device allocation of partial images failed");
+    }
+    return BF_OK;
+}
+
+// Configure one frame, build its device tables and upload them.  own: the frame
+// runs launches of its own (a plan's first frame).
+int Frame::init(const bf_params &src, bool own)
 {
     configure(src);
     const int n = p.n_tx;
@@ -352,9 +364,9 @@ int Frame::init(const bf_params &src)
         hipError_t he = hipMemcpy(d_hann, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
         if (he != hipSuccess) return hip_fail(he, "upload of the Hann table");
     }
-    if (groups > 1) {
-        d_part = (float *)alloc((size_t)groups * out_elems() * sizeof(float));
-        if (!d_part) return fail(BF_ERR_HIP, "device allocation of partial images failed");
+    if (own) {
+        const int st = alloc_part();
+        if (st != BF_OK) return st;
     }
     if (!d_At || !d_colsum || !d_Hf || !d_tx_x || !d_rx_c || !d_partial)
         return fail(BF_ERR_HIP, "device allocation for plan tables failed");
@@ -423,6 +435,10 @@ void Frame::choose_box()
     }
 }
 
+// Largest partial images of a plan.  The baseband volume of 64 x 64 x 128 points
+// takes 32 MiB for its 8 groups (DAS 1 009 us; 2 groups, 8 MiB, 1 472 us).
+constexpr long PART_MAX_BYTES = 32l << 20;
+
 // Channel groups: small grids give too few workgroups to fill 256 CUs, so the
 // channel sum is split over `groups` workgroup sets whose partial images are
 // added in a fixed order afterwards.
@@ -461,7 +477,7 @@ void Frame::choose_box()
 //    balance gains.  Another split, down to 96 traces, is taken where its rounds
 //    are 20 % cheaper: over 150 volumes 2.4 % slower than the best split timed,
 //    4.0 without this, 13.4 with the floor.
-// The partial images stay within BF_DAS_NOALLOC_MAX_BYTES.
+// The partial images stay within PART_MAX_BYTES.
 void Frame::choose_groups()
 {
     const long nvox = (long)grid.nx * grid.ny * grid.nz;
@@ -474,7 +490,7 @@ void Frame::choose_groups()
     if (p.mode == BF_FORCES_2D && p.e_type == BF_E_F32 && !p.iq) return;
     const long boxes = (long)c.blocks_x * c.blocks_y * c.blocks_z;
     const long slots = 512;
-    const long cap = std::max<long>(1, BF_DAS_NOALLOC_MAX_BYTES / (out_elems() * (long)sizeof(float)));
+    const long cap = std::max<long>(1, PART_MAX_BYTES / (out_elems() * (long)sizeof(float)));
     const int chunks = (p.n_ch + JC - 1) / JC;
     auto chunks_of = [&](long g) { return (double)((chunks + g - 1) / g); };
     // rounds of the fullest XCD with g groups: the last, partial one costs `last`
@@ -997,8 +1013,8 @@ int Frame::das_adjoint(const void *e, const float *grad_out, double c, float *gr
 }
 
 // ---------------------------------------------------------------------------
-// Scratch of bf_das_noalloc: the partial images of a channel-split DAS launch
-// live in this file-scope device array instead of plan memory.  Each device
+// Scratch of bf_das_noalloc: the partial images of a channel-split DAS launch, if
+// they fit, live in this file-scope device array instead of plan memory.  Each device
 // holds its own copy (at its own address) for the life of the process.  Host
 // code never passes the array's name to a kernel (on the host it is only a
 // stand-in for the symbol): the device address is looked up once per device
@@ -1086,7 +1102,7 @@ int bf_plan_create_batch(const bf_params *params, int32_t n_frames, bf_plan *out
     plan->frames.resize(n_frames);
     for (int f = 0; f < n_frames; ++f) {
         plan->frames[f] = new Frame();
-        st = plan->frames[f]->init(params[f]);
+        st = plan->frames[f]->init(params[f], f == 0);
         if (st != BF_OK) {
             delete plan;
             return st;
@@ -1229,14 +1245,11 @@ int bf_das_noalloc(bf_plan plan, const void *e, float *out, double c, void *stre
         return fail(BF_ERR_STATE, "current device %d is not the plan's device %d", dev,
                     plan->device);
     const Frame &f = *plan->frames[0];
-    float *part = nullptr;
-    if (f.groups > 1) {
-        const uint64_t need = (uint64_t)f.groups * (uint64_t)f.out_elems() * sizeof(float);
-        if (need > BF_DAS_NOALLOC_MAX_BYTES)
-            return fail(BF_ERR_TOO_LARGE, "partial images need %llu bytes, the scratch holds %u",
-                        (unsigned long long)need, (unsigned)BF_DAS_NOALLOC_MAX_BYTES);
-        if ((st = scratch_ptr(dev, &part)) != BF_OK) return st;
-    }
+    float *part = nullptr;      // (larger partial images: the plan's own)
+    if (f.groups > 1 &&
+        (uint64_t)f.groups * (uint64_t)f.out_elems() * sizeof(float) <= BF_DAS_NOALLOC_MAX_BYTES &&
+        (st = scratch_ptr(dev, &part)) != BF_OK)
+        return st;
     return f.das(e, out, c, (hipStream_t)stream, part);
 }
 

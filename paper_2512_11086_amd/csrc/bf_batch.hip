@@ -170,6 +170,8 @@ static int build_batch(bf_plan plan)
         fi.das_items = 0;
         if (!lds_ok[f] || !fr.lds_config(a, &c)) {
             b->gather_frames.push_back(f);
+            const int st = fr.alloc_part();
+            if (st != BF_OK) return st;
             memset(&c, 0, sizeof c);
         } else if (groups[f] > 1 &&
                    (long)c.blocks_x * c.blocks_y * c.blocks_z * fr.adj_groups >= 2L * cus0) {
@@ -181,6 +183,8 @@ static int build_batch(bf_plan plan)
             // persistent launch (a pair of 256 x 256 planes from 128 x 128
             // traces: 1.35 ms per pass persistent).
             b->frame_lds.push_back(f);
+            const int st = fr.alloc_part();
+            if (st != BF_OK) return st;
             fi.das_path = BF_BATCH_FRAME_LDS;
             fi.channel_groups = fr.groups;
             fi.das_items = (int64_t)c.blocks_x * c.blocks_y * c.blocks_z * fr.groups;
@@ -648,6 +652,8 @@ int bf_autotune(bf_plan plan, const char *cache_path)
         TileCand best{};
         bool have = cache_path && cache_lookup(cache_path, key, &best);
         if (!have) {
+            const int st = f0->alloc_part();
+            if (st != BF_OK) return st;
             void *e_buf = nullptr;
             float *o_buf = nullptr;
             const size_t o_bytes = (size_t)f0->out_elems() * 4;

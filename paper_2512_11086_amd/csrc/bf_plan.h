@@ -37,7 +37,7 @@ struct Frame {
     int groups = 1;              // channel groups of the DAS launch (small grids)
     int adj_groups = 1;          // channel groups of the adjoint launches
     int stack_cap = 0;           // frames per adjoint launch of a stack (0: no cap)
-    float *d_part = nullptr;     // [groups][points] partial images
+    float *d_part = nullptr;     // [groups][points] partial images (alloc_part)
     float2 *d_hann = nullptr;    // Hann weight table (HANN_N + 1 entries)
     long max_blocks = 0;
     int8_t *d_At = nullptr;
@@ -53,7 +53,8 @@ struct Frame {
     ~Frame();
     void *alloc(size_t bytes);
     void configure(const bf_params &src, int allowed = 3);
-    int init(const bf_params &src);
+    int init(const bf_params &src, bool own);
+    int alloc_part();
     void set_tile(int lx, int ly, int lz);
     void find_mirrors();
     void choose_box();

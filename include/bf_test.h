@@ -31,6 +31,11 @@ int bf_test_set_stack_cap(bf_plan plan, int32_t cap);
  * compare mirrored launches with plain ones. */
 int bf_test_set_mirrors(bf_plan plan, int32_t allowed);
 
+/* Run a demodulator's calls on the vector units (unit 1), on the matrix cores (2,
+ * where its filter fits them) or where the library's rule puts them (0); returns
+ * the unit they then run on, 1 or 2. */
+int bf_test_demod_unit(bf_demod d, int32_t unit);
+
 /* The launch bf_das would make for a description, on the host alone (no device
  * is needed), with the mirror axes restricted to `allowed`: lds = 0 is the
  * gather kernel; nb counts the traces per batch and mirror copy, mirrors the

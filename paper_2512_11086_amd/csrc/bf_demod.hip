@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "bf.h"
+#include "bf_test.h"
 #include "bf_common.h"
 #include "bf_plan.h"
 
@@ -402,6 +403,7 @@ struct bf_demod_s {
     bf_demod_params p;
     int n_out = 0;
     int kind[16];
+    int unit = 0;         // 0: by rule; 1: vector units, 2: matrix cores (tests)
     float2 *d_g = nullptr;
     float2 *d_rot = nullptr;
     ~bf_demod_s()
@@ -459,45 +461,71 @@ static void launch_mfma_t(const DemodArgs &a, const DemodTile &m, int out_type, 
         hipLaunchKernelGGL((demod_mfma_kernel<BF_IQ_F32, T>), grid, dim3(256), shm, s, a, m);
 }
 
-// Launches the matrix-core kernel where it is the faster one: for filters of
-// 61 taps and more, for decimations from 3 (whose staging splits into words
-// of components on the vector units), and from 2^23 outputs on from 32 / D
-// taps.  Vector units against matrix cores, us, D = 1 / 2 / 4: 16 384 x 2816
-// samples, 16 taps 106 129 / 82 76 / 58 57, 36 taps 142 131 / 103 77 / 75 61,
-// 166 taps 482 317 / 305 119 / 165 96; 4096 x 2047 samples, 36 taps 29 33 / 18
-// 21 / 24 17, 100 taps 56 49 / 29 25 / 33 21.
+// Where the matrix-core kernel is the faster one.
+//  - D <= 2: for filters of 61 taps and more, and from 2^23 outputs on from 32 / D
+//    taps.  Vector units against matrix cores, us, D = 1 / 2: 16 384 x 2816
+//    samples, 16 taps 106 129 / 82 76, 36 taps 142 131 / 103 77, 166 taps 482 317
+//    / 305 119; 4096 x 2047 samples, 36 taps 29 33 / 18 21, 100 taps 56 49 / 29 25.
+//  - D >= 3: the vector kernel takes a workgroup per trace, and stages D words a
+//    time per output; it is the faster one for few traces (up to 590, 1500 at D =
+//    16, unless a component has more than 20 taps), where either is bound by the
+//    latency of one workgroup (194 x 1501 samples, D = 12, 49 taps 13.7 16.6), and
+//    for records of more than 640 outputs with short filters (1588 x 2816, D = 3,
+//    22 taps 12.9 14.9).  Elsewhere the matrix cores win: 16 384 x 2816, D = 4, 36
+//    taps 75 61, 166 taps 165 96; 4796 x 300, D = 6, 6 taps 34 11.  1 751 filters
+//    (D 3 to 16, 1 to 169 taps, 64 to 16 384 traces of 300 to 2816 samples): 1.0 %
+//    slower than the faster unit on average; the matrix cores alone 2.4, the
+//    vector units 57.
+static bool matrix_cores_faster(const bf_demod_params &p, int n_out)
+{
+    const int D = p.decimation;
+    if (D <= 2)
+        return p.n_taps >= 61 || ((long)p.n_traces * n_out >= (1L << 23) && p.n_taps * D >= 32);
+    if (p.n_taps > 20 * D) return true;
+    if (p.n_traces <= (D >= 16 ? 1500 : 590)) return false;
+    return n_out <= 640 || p.n_taps >= 61 || (p.n_traces > 3000 && p.n_taps >= 16);
+}
+
+// Tiles per wavefront of the matrix-core launch (0: the vector units run), its
+// tile and chunks of a trace, and its LDS.
 // T = 2 tiles per wavefront (4 measured 10 % slower, its accumulators halve
 // the occupancy; 1 up to 20 %), 1 where that leaves fewer than 1024 workgroups
 // or two tiles' samples exceed 64 KiB.
-static bool launch_demod_mfma(bf_demod d, DemodArgs a, hipStream_t s)
+static int mfma_tiles(bf_demod d, DemodTile *m, int *chunks, size_t *shm)
 {
-    const bool large = (long)a.n_traces * a.n_out >= (1L << 23) && a.n_taps * a.D >= 32;
-    if (a.n_taps < 61 && a.D < 3 && !large) return false;
-    DemodTile m;
-    m.groups = (a.n_traces + DEMOD_TR - 1) / DEMOD_TR;
+    const int D = d->p.decimation, n_taps = d->p.n_taps;
+    if (d->unit == 1 || (d->unit == 0 && !matrix_cores_faster(d->p, d->n_out))) return 0;
+    m->groups = (d->p.n_traces + DEMOD_TR - 1) / DEMOD_TR;
     int nbmax = 0, tap_words = 0;
-    for (int ph = 0; ph < a.D; ++ph) {
-        const int nb = phase_taps(a.n_taps, a.D, ph);
+    for (int ph = 0; ph < D; ++ph) {
+        const int nb = phase_taps(n_taps, D, ph);
         tap_words += toeplitz_taps(nb);
         nbmax = std::max(nbmax, nb);
     }
     for (int T = 2; T >= 1; --T) {
         const int words = 64 * T - 16 + toeplitz_cols(nbmax);
-        m.rows8 = (a.D * words + 7 + 7) / 8;
-        m.inv_rows8 = 1.f / (float)m.rows8;
-        m.stride = ((8 * m.rows8 + 127) & ~127) + 8;
-        const size_t shm = (size_t)DEMOD_TR * m.stride * 2 + (size_t)tap_words * 8;
-        a.chunks = (a.n_out + 64 * T - 1) / (64 * T);
-        const long blocks = (long)m.groups * a.chunks;
-        if (T == 2 && (shm > 64 * 1024 || blocks < 1024)) continue;
-        if (shm > 64 * 1024 || blocks >= (1L << 31)) return false;
-        if (T == 2)
-            launch_mfma_t<2>(a, m, d->p.out_type, shm, s);
-        else
-            launch_mfma_t<1>(a, m, d->p.out_type, shm, s);
-        return true;
+        m->rows8 = (D * words + 7 + 7) / 8;
+        m->inv_rows8 = 1.f / (float)m->rows8;
+        m->stride = ((8 * m->rows8 + 127) & ~127) + 8;
+        *shm = (size_t)DEMOD_TR * m->stride * 2 + (size_t)tap_words * 8;
+        *chunks = (d->n_out + 64 * T - 1) / (64 * T);
+        const long blocks = (long)m->groups * *chunks;
+        if (T == 2 && (*shm > 64 * 1024 || blocks < 1024)) continue;
+        return *shm > 64 * 1024 || blocks >= (1L << 31) ? 0 : T;
     }
-    return false;
+    return 0;
+}
+
+static bool launch_demod_mfma(bf_demod d, DemodArgs a, hipStream_t s)
+{
+    DemodTile m;
+    size_t shm = 0;
+    const int T = mfma_tiles(d, &m, &a.chunks, &shm);
+    if (T == 2)
+        launch_mfma_t<2>(a, m, d->p.out_type, shm, s);
+    else if (T == 1)
+        launch_mfma_t<1>(a, m, d->p.out_type, shm, s);
+    return T != 0;
 }
 
 extern "C" {
@@ -639,6 +667,19 @@ int bf_demodulate(bf_demod d, const int16_t *rf, void *iq, void *stream)
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BF_OK : hip_fail(e, "demodulation launch");
+}
+
+int bf_test_demod_unit(bf_demod d, int32_t unit)
+{
+    clear_err();
+    if (!d) return fail(BF_ERR_NULL, "demodulator is NULL");
+    if (d->magic != 0xBFDE0D01u) return fail(BF_ERR_STATE, "not a live demodulator");
+    if (unit < 0 || unit > 2) return fail(BF_ERR_UNSUPPORTED, "unknown unit %d", unit);
+    d->unit = unit;
+    DemodTile m;
+    int chunks = 0;
+    size_t shm = 0;
+    return mfma_tiles(d, &m, &chunks, &shm) ? 2 : 1;
 }
 
 }  // extern "C"

@@ -519,13 +519,42 @@ std::vector<TileCand> candidates(const Frame &f)
     return c;
 }
 
+// Mirror axes are part of a problem's shape: points per lane, batches and LDS
+// layout follow from them (plans without any keep the key they had).
 std::string tune_key(const Frame &f, const char *arch)
 {
-    char buf[256];
-    snprintf(buf, sizeof buf, "%s|m%d|tx%d|ch%d|S%d|%dx%dx%d|ip%d|et%d%s", arch, f.p.mode,
+    char buf[256], mir[16] = "";
+    if (f.mirrors) snprintf(mir, sizeof mir, "|mir%d", f.mirrors);
+    snprintf(buf, sizeof buf, "%s|m%d|tx%d|ch%d|S%d|%dx%dx%d|ip%d|et%d%s%s", arch, f.p.mode,
              f.p.n_tx, f.p.n_ch, f.p.n_samples, f.grid.nx, f.grid.ny, f.grid.nz, f.p.interp,
-             f.p.e_type, f.p.iq ? "|iq" : "");
+             f.p.e_type, f.p.iq ? "|iq" : "", mir);
     return buf;
+}
+
+void set_config(Frame *f, const TileCand &t)
+{
+    f->set_tile(t.lx, t.ly, t.lz);
+    f->bw[0] = t.bwx;
+    f->bw[1] = t.bwy;
+    f->bw[2] = t.bwz;
+    f->nb = t.nb;
+    f->variant = t.variant;
+}
+
+// Gives a frame the configuration of its class (tuned on another frame, or read
+// from the cache: another grid or aperture of the same shape), unless that takes
+// the frame's LDS kernel from it or, in a batch, its kernel class.
+void apply_config(Frame *f, const TileCand &t, bool batch)
+{
+    const TileCand own{f->lx, f->ly, f->lz, f->bw[0], f->bw[1], f->bw[2], f->nb, f->variant};
+    LdsCfg before, after;
+    const bool lds = f->variant != BF_DAS_GATHER &&
+                     f->lds_config(f->das_args(nullptr, nullptr, f->p.c), &before);
+    set_config(f, t);
+    if (!lds || t.variant == BF_DAS_GATHER) return;
+    if (!f->lds_config(f->das_args(nullptr, nullptr, f->p.c), &after) ||
+        (batch && mirror_copies(after.mir) != mirror_copies(before.mir)))
+        set_config(f, own);
 }
 
 bool cache_lookup(const char *path, const std::string &key, TileCand *out)
@@ -687,12 +716,7 @@ int bf_autotune(bf_plan plan, const char *cache_path)
             for (const TileCand &t : cands) {
                 if (batch && (t.bwx * t.bwy * t.bwz != threads0 || t.variant != saved_variant))
                     continue;
-                f0->set_tile(t.lx, t.ly, t.lz);
-                f0->bw[0] = t.bwx;
-                f0->bw[1] = t.bwy;
-                f0->bw[2] = t.bwz;
-                f0->nb = t.nb;
-                f0->variant = t.variant;
+                set_config(f0, t);
                 LdsCfg cfg;
                 if (t.variant != BF_DAS_GATHER &&
                     !f0->lds_config(f0->das_args(e_buf, o_buf, f0->p.c), &cfg))
@@ -715,6 +739,7 @@ int bf_autotune(bf_plan plan, const char *cache_path)
             (void)hipEventDestroy(t1);
             (void)hipFree(e_buf);
             (void)hipFree(o_buf);
+            set_config(f0, cands[0]);
             if (best_ms >= 1e30f)
                 best = {saved[0], saved[1], saved[2], saved[3], saved[4], saved[5], saved[6],
                         saved_variant};
@@ -729,13 +754,7 @@ int bf_autotune(bf_plan plan, const char *cache_path)
         }
         for (size_t f = c0; f < plan->frames.size(); ++f)
             if (keys[f] == key) {
-                Frame *fr = plan->frames[f];
-                fr->set_tile(best.lx, best.ly, best.lz);
-                fr->bw[0] = best.bwx;
-                fr->bw[1] = best.bwy;
-                fr->bw[2] = best.bwz;
-                fr->nb = best.nb;
-                fr->variant = best.variant;
+                apply_config(plan->frames[f], best, batch);
                 done[f] = 1;
             }
     }

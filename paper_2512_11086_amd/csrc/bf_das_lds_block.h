@@ -872,58 +872,51 @@ __device__ inline void hercules_term(const LaneL (&L)[ZP], const float4 *win, in
     const float dx = L[0].x - xi;
     const float rho2 = fmaf(dx, dx, dy2);
     if constexpr (HF) {
-        // Up to four 16-byte reads (and their points' Hann entries) are issued
+        // Up to four 16-byte reads of a point (and its Hann entry) are issued
         // together before the first is used: a scheduling barrier keeps the
         // compiler from pairing each read with its own wait, which serialized
         // a wavefront on the latency of every read.
         constexpr unsigned MS = mirror_set_quads(NM) * 16;
         constexpr int QS = ET == ET_CF32 ? 2 : 1;
         constexpr int MG = NM * QS <= 4 ? NM : 4 / QS;        // copies per group of reads
-        constexpr int PG = 1;
 #pragma unroll
-        for (int p0 = 0; p0 < ZP; p0 += PG) {
-            float s[PG], xw[PG];
-            float2 h[PG], r[PG];
-            unsigned ad[PG];
-            float4 q[PG * MG * QS];
+        for (int p = 0; p < ZP; ++p) {
+            const LaneL &l = L[p];
+            float s, xw;
+            float2 h, r;
+            unsigned ad;
+            float4 q[MG * QS];
 #pragma unroll
             for (int m0 = 0; m0 < NM; m0 += MG) {
-#pragma unroll
-                for (int u = 0; u < PG; ++u) {
-                    const LaneL &l = L[p0 + u];
-                    if (m0 == 0) {
-                        const float dk = __builtin_amdgcn_sqrtf(fmaf(rho2, ik2, l.zk2));
-                        s[u] = fmaf(rho2, __builtin_amdgcn_rcpf(dk + l.zk), l.fB);
-                        xw[u] = __builtin_amdgcn_fmed3f(rho2 * l.wtab, 0.f, 1.f);
-                        h[u] = hann_entry(hann, xw[u]);
-                        if constexpr (QS == 2)
-                            ad[u] = ((unsigned)(cvt_flr(s[u]) + l.nB) << 5) + (unsigned)neg_w0;
-                        else
-                            ad[u] = ((unsigned)cvt_flr(s[u]) << 4) + (unsigned)neg_w0;
-                    }
-#pragma unroll
-                    for (int m = 0; m < MG; ++m)
-#pragma unroll
-                        for (int c = 0; c < QS; ++c)
-                            q[(u * MG + m) * QS + c] = lds_read_f4(ad[u] + (m0 + m) * MS + 16 * c);
+                if (m0 == 0) {
+                    const float dk = __builtin_amdgcn_sqrtf(fmaf(rho2, ik2, l.zk2));
+                    s = fmaf(rho2, __builtin_amdgcn_rcpf(dk + l.zk), l.fB);
+                    xw = __builtin_amdgcn_fmed3f(rho2 * l.wtab, 0.f, 1.f);
+                    h = hann_entry(hann, xw);
+                    if constexpr (QS == 2)
+                        ad = ((unsigned)(cvt_flr(s) + l.nB) << 5) + (unsigned)neg_w0;
+                    else
+                        ad = ((unsigned)cvt_flr(s) << 4) + (unsigned)neg_w0;
                 }
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+#pragma unroll
+                    for (int c = 0; c < QS; ++c)
+                        q[m * QS + c] = lds_read_f4(ad + (m0 + m) * MS + 16 * c);
                 __builtin_amdgcn_sched_barrier(0);
+                const float t = __builtin_amdgcn_fractf(s);
+                if (m0 == 0) {
+                    r.x = fmaf(xw, h.y, h.x);
+                    if constexpr (QS == 2) r = rotation(r.x, fmaf(rot, s, l.ph0));
+                }
 #pragma unroll
-                for (int u = 0; u < PG; ++u) {
-                    const float t = __builtin_amdgcn_fractf(s[u]);
-                    if (m0 == 0) {
-                        r[u].x = fmaf(xw[u], h[u].y, h[u].x);
-                        if constexpr (QS == 2) r[u] = rotation(r[u].x, fmaf(rot, s[u], L[p0 + u].ph0));
-                    }
-#pragma unroll
-                    for (int m = 0; m < MG; ++m) {
-                        float2 &o = acc[(m0 + m) * ZP + p0 + u];
-                        const float4 *v = q + (u * MG + m) * QS;
-                        if constexpr (QS == 2)
-                            rotate_add(make_float2(eval_quad<IP>(v[0], t), eval_quad<IP>(v[1], t)), r[u], o);
-                        else
-                            o.x = fmaf(r[u].x, eval_quad<IP>(v[0], t), o.x);
-                    }
+                for (int m = 0; m < MG; ++m) {
+                    float2 &o = acc[(m0 + m) * ZP + p];
+                    const float4 *v = q + m * QS;
+                    if constexpr (QS == 2)
+                        rotate_add(make_float2(eval_quad<IP>(v[0], t), eval_quad<IP>(v[1], t)), r, o);
+                    else
+                        o.x = fmaf(r.x, eval_quad<IP>(v[0], t), o.x);
                 }
             }
         }

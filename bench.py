@@ -95,7 +95,7 @@ def mirror_copies(plan) -> int:
     """Points that share a term's delay and weight in the plan's DAS launch
     (mirror points: 1, 2 or 4)."""
     from paper_2512_11086_amd import _lib
-    axes = _lib.lib().bf_test_set_mirrors(plan._h, 3)     # (3: every axis stays allowed)
+    axes = _lib.lib().bf_test_mirror_axes(plan._h)
     return {0: 1, 1: 2, 2: 2, 3: 4}[axes]
 
 

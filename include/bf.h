@@ -415,12 +415,14 @@ int bf_demodulate(bf_demod d, const int16_t *rf, void *iq, void *stream);
  *   (computed on the device; an all-zero image gives -param / 0).
  * img: device f32 [n_cols][n] (depth fastest: a [Ny][Nx][Nz] volume has
  * n_cols = Ny*Nx, n = Nz) or, for iq = 1, complex f32 [n_cols][n][2];
- * out: device f32 [n_cols][n] (must not overlap img).  FP32 arithmetic: for
- * power-of-two n from 64 to 1024 a register-resident FFT per pair of columns
- * (two real columns as one complex transform: the inverse DFT of
- * -j sgn(k) DFT(x1 + j x2) is H{x1} + j H{x2}, and env = sqrt(x^2 + H{x}^2));
- * other powers of two a radix-2 FFT in LDS; other n from 24 to 1000 a circulant
- * product on the matrix cores; a direct circular sum otherwise.
+ * out: device f32 [n_cols][n]; it may be img itself (iq = 0), but not overlap it
+ * otherwise.  FP32 arithmetic: for n = 64, 128 and 256 an FFT per pair of columns
+ * inside the lanes with two transpositions through LDS, for 512 and 1024 one
+ * across a wavefront's lanes in registers (two real columns as one complex
+ * transform: the inverse DFT of -j sgn(k) DFT(x1 + j x2) is H{x1} + j H{x2}, and
+ * env = sqrt(x^2 + H{x}^2)); other powers of two a radix-2 FFT in LDS; other n
+ * from 24 to 1000 a circulant product on the matrix cores; a direct circular sum
+ * otherwise.
  * A plan holds its tables and a partial-maximum buffer, so calls of one plan
  * must not overlap on the device.
  * ------------------------------------------------------------------------- */

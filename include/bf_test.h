@@ -30,6 +30,8 @@ int bf_test_set_stack_cap(bf_plan plan, int32_t cap);
  * batched launch) and return the axes its frames then use, so that tests can
  * compare mirrored launches with plain ones. */
 int bf_test_set_mirrors(bf_plan plan, int32_t allowed);
+/* The mirror axes the frames of a plan use. */
+int bf_test_mirror_axes(bf_plan plan);
 
 /* Run a demodulator's calls on the vector units (unit 1), on the matrix cores (2,
  * where its filter fits them) or where the library's rule puts them (0); returns

@@ -121,6 +121,7 @@ def lib():
         "bf_test_hann_poly": ([dbl], dbl),
         "bf_test_set_stack_cap": ([vp, i32], ctypes.c_int),
         "bf_test_set_mirrors": ([vp, i32], ctypes.c_int),
+        "bf_test_mirror_axes": ([vp], ctypes.c_int),
         "bf_test_demod_unit": ([vp, i32], ctypes.c_int),
         "bf_test_das_launch": ([P(Params), i32, P(TestLaunch)], ctypes.c_int),
         "bf_demod_create": ([P(DemodParams), P(vp)], ctypes.c_int),
@@ -156,6 +157,6 @@ EXPORTED = ("bf_abi_version", "bf_last_error", "bf_validate", "bf_plan_create",
             "bf_demod_destroy", "bf_demod_out_samples", "bf_demodulate", "bf_env_create",
             "bf_env_destroy", "bf_envelope")
 TEST_HOOKS = ("bf_test_hann_poly", "bf_test_set_stack_cap", "bf_test_set_mirrors",   # include/bf_test.h
-              "bf_test_das_launch", "bf_test_demod_unit")
+              "bf_test_das_launch", "bf_test_demod_unit", "bf_test_mirror_axes")
 COMPRESS = {"none": 0, "log": 1, "power": 2}
 VARIANTS = {"lds": 0, "gather": 1, "lds2": 2}   # BF_DAS_LDS, BF_DAS_GATHER, BF_DAS_LDS_Z2

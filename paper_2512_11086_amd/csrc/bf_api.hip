@@ -1304,19 +1304,27 @@ int bf_sharpness(const float *img, int64_t n_per_image, int32_t n_images, float 
 
 double bf_test_hann_poly(double u2) { return (double)hann_u2((float)u2); }
 
-int bf_test_set_mirrors(bf_plan plan, int32_t allowed)
+int bf_test_mirror_axes(bf_plan plan)
 {
     g_err.clear();
     int st = check_plan(plan);
     if (st != BF_OK) return st;
     int used = 0;
-    for (Frame *f : plan->frames) {
-        f->mirrors &= allowed;
+    for (const Frame *f : plan->frames) {
         LdsCfg cfg;
         if (f->variant != BF_DAS_GATHER && f->lds_config(f->das_args(nullptr, nullptr, f->p.c), &cfg))
             used |= cfg.mir;
     }
     return used;
+}
+
+int bf_test_set_mirrors(bf_plan plan, int32_t allowed)
+{
+    g_err.clear();
+    int st = check_plan(plan);
+    if (st != BF_OK) return st;
+    for (Frame *f : plan->frames) f->mirrors &= allowed;
+    return bf_test_mirror_axes(plan);
 }
 
 int bf_test_das_launch(const bf_params *params, int32_t allowed, bf_test_launch *out)

@@ -41,9 +41,10 @@ int bf_test_demod_unit(bf_demod d, int32_t unit);
 /* The launch bf_das would make for a description, on the host alone (no device
  * is needed), with the mirror axes restricted to `allowed`: lds = 0 is the
  * gather kernel; nb counts the traces per batch and mirror copy, mirrors the
- * axes used, blocks the workgroup boxes along x, y and z. */
+ * axes used, blocks the workgroup boxes along x, y and z, refs the delay
+ * references of a box. */
 typedef struct {
-    int32_t lds, mirrors, nb, zp, tile[3], block[3], blocks[3], lmax, groups, adj_groups;
+    int32_t lds, mirrors, nb, zp, tile[3], block[3], blocks[3], lmax, groups, adj_groups, refs;
 } bf_test_launch;
 int bf_test_das_launch(const bf_params *params, int32_t allowed, bf_test_launch *out);
 

@@ -78,7 +78,7 @@ class TestLaunch(ctypes.Structure):
     _fields_ = [("lds", ctypes.c_int32), ("mirrors", ctypes.c_int32), ("nb", ctypes.c_int32),
                 ("zp", ctypes.c_int32), ("tile", ctypes.c_int32 * 3), ("block", ctypes.c_int32 * 3),
                 ("blocks", ctypes.c_int32 * 3), ("lmax", ctypes.c_int32), ("groups", ctypes.c_int32),
-                ("adj_groups", ctypes.c_int32)]
+                ("adj_groups", ctypes.c_int32), ("refs", ctypes.c_int32)]
 
 
 BATCH_PATHS = {0: "persistent_lds", 1: "gather", 2: "frame_lds"}

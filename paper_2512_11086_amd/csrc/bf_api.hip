@@ -392,22 +392,12 @@ int Frame::init(const bf_params &src, bool own)
 // 48 x 48 x 96 from 64 x 128 traces 932, 851; 49 x 109 x 120 from 24 x 128 1 290,
 // 1 160; IQ 32 x 24 x 144 from 20 x 116 376, 300; IQ 118 x 128 x 71 from 20 x 64
 // 969, 846.  The count is good to about 5 %, so a shape has to be 6 % better.
-//
-// With real data the lanes' positions are FP32 numbers relative to a reference in
-// the middle of the box's delays, and lose bits of their fraction as these
-// spread: a box is deeper than the default's only while the delays of its
-// depths stay within 16 samples of the reference (position error, emulated, RMS
-// in samples, boxes of 6, 8 and 24 depths: steps of 3.8 samples 1.38, 1.39 and
-// 1.64e-6; 20.7 samples 1.74, 2.16 and 5.05e-6).  IQ lanes keep their integer
-// sample apart.
 void Frame::choose_box()
 {
     if (p.mode != BF_HERCULES_3D || variant == BF_DAS_GATHER || p.interp == BF_INTERP_NEAREST) return;
     const int tiles[3][3] = {{3, 3, 0}, {2, 3, 1}, {3, 2, 1}};
     const int blocks[3][3] = {{2, 2, 3}, {3, 2, 2}, {2, 1, 6}};
     const int lx0 = lx, ly0 = ly, lz0 = lz, bw0[3] = {bw[0], bw[1], bw[2]};
-    const int deepest = (bw[2] << lz) * (variant == BF_DAS_LDS_Z2 && z2_ok() ? 2 : 1);
-    const double step = 2.0 * p.fs / p.c * fabs(grid.az[2]);     // samples per depth
     double best = 1e300, first = 1e300;
     int bt = 0, bb = 0;
     for (int t = 0; t < 3; ++t)
@@ -416,8 +406,6 @@ void Frame::choose_box()
             for (int r = 0; r < 3; ++r) bw[r] = blocks[b][r];
             LdsCfg c;
             if (!lds_config(das_args(nullptr, nullptr, p.c), &c)) continue;
-            const int depths = (bw[2] << lz) * c.zp;
-            if (!p.iq && depths > deepest && 0.5 * step * (depths - 1) > 16.0) continue;
             const double cost = launch_cost(c);
             if (t == 0 && b == 0) first = cost;
             if (cost < best) {
@@ -730,6 +718,17 @@ bool Frame::fit_config(const DasArgs &a, int mir, LdsCfg *cfg, int adj, const in
     // half as deep balance better)
     const int zp = variant == BF_DAS_LDS_Z2 && z2_ok() && nm == 1 ? 2 : 1;
     const int tz = (bw[2] << lz) * zp;
+    // Positions of real HERCULES data are FP32 numbers relative to a reference in
+    // the middle of the box's delays, and lose bits of their fraction as these
+    // spread (position error, emulated, RMS in samples, boxes of 6, 8 and 24
+    // depths: steps of 3.8 samples 1.38, 1.39 and 1.64e-6; 20.7 samples 1.74, 2.16
+    // and 5.05e-6).  A box deeper than the default's 6 depths, and more than 16
+    // samples from its reference, has one for each row of wavefronts along z
+    // instead (4 depths at most in the shapes of choose_box).
+    const double step = 2.0 * a.k * grid.az[2];     // samples per depth
+    const bool deep = !sep && !p.iq && adj == 0 && tz > 6 && 0.5 * fabs(step) * (tz - 1) > 16.0;
+    cfg->refs = deep ? bw[2] : 1;
+    cfg->ref_step = (float)step;
     // VLS: the transmit path jumps at the virtual line's depth (converging
     // above it, diverging below), so no box may hold points of both sides:
     // the box grid is shifted along z to start a box where the side changes.
@@ -805,7 +804,7 @@ bool Frame::fit_config(const DasArgs &a, int mir, LdsCfg *cfg, int adj, const in
     const int qs = p.iq ? 2 : 1;
     const bool staged = adj == 0 || (adj & 1);    // the RF gradient alone reads no data
     while (nbb >= unit && ((staged && rounds(nbb) > max_rounds) ||
-                           lds_bytes(p.n_tx, p.n_ch, nbb, lmax, qs, guard, adj, p.mode, nm) > lds_cap))
+                           lds_bytes(p.n_tx, p.n_ch, nbb, lmax, qs, guard, adj, p.mode, nm, cfg->refs) > lds_cap))
         nbb -= unit;
     if (nbb < unit || nthr > 1024) return false;
     // A launch with at most one workgroup per CU (a small plane, a row-column
@@ -1355,6 +1354,7 @@ int bf_test_das_launch(const bf_params *params, int32_t allowed, bf_test_launch 
     out->blocks[1] = c.blocks_y;
     out->blocks[2] = c.blocks_z;
     out->lmax = c.lmax;
+    out->refs = c.refs;
     return BF_OK;
 }
 

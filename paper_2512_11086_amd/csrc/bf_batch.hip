@@ -199,7 +199,7 @@ static int build_batch(bf_plan plan)
             }
             const int threads = 64 * c.bwx * c.bwy * c.bwz;
             const int nm = mirror_copies(c.mir);
-            const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, 1, c.guard, 0, fr.p.mode, nm);
+            const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, 1, c.guard, 0, fr.p.mode, nm, c.refs);
             DasClass *cls = nullptr;
             for (DasClass &d : b->das)
                 if (d.mode == fr.p.mode && d.et == fr.p.e_type && d.ip == fr.p.interp &&

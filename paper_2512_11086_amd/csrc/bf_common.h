@@ -139,6 +139,8 @@ struct LdsCfg {
                          // (HERCULES: reads of lanes outside their aperture)
     int ex, ey;          // grid columns and rows the boxes cover (a mirrored axis: its lower half)
     int mir;             // MIRROR_*: the axis along which a lane also computes the mirror points
+    int refs;            // references of a box's delays (HERCULES real data): 1, or bwz, one per
+    float ref_step;      // row of wavefronts along z; samples per depth (box_ref)
 };
 
 // Mirrored HERCULES launches (das_block, NM = 2 or 4): the aperture and the

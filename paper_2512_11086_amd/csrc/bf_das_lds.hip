@@ -202,12 +202,12 @@ static hipError_t launch_lds_et(const DasArgs &a, const LdsCfg &c, int et, int i
 hipError_t launch_das_lds_fused(const DasArgs &a, const LdsCfg &c, int ip, hipStream_t s);
 
 size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
-                 int nm)
+                 int nm, int refs)
 {
     const bool stage = adj == 0 || (adj & 1);     // data windows staged
     // tx_x and rx_c (and the separable modes' path bounds: one more of each)
     const int tables = (mode == MODE_HERCULES ? 1 : 2) * (((n_tx + 3) & ~3) + ((n_ch + 3) & ~3));
-    return (size_t)(tables + 2 * ((nb + 3) & ~3)) * 4 +
+    return (size_t)(tables + 2 * refs * ((nb + 3) & ~3)) * 4 +
            (mode == MODE_HERCULES ? (size_t)HANN_TAB_PAD * 8 : 0) +
            (stage ? (2 * (size_t)(nm > 1 ? nm * mirror_set_quads(nm) : nb * lmax * qs) + guard * qs) * 16 : 0) +
            ((adj & 2) ? 2 * (size_t)nb * (lmax + 3) * 8 + 16 * 4 : 0);
@@ -225,7 +225,7 @@ hipError_t launch_das_lds(const DasArgs &a, const LdsCfg &c, int mode, int et, i
                           hipStream_t s)
 {
     const size_t shm = lds_bytes(a.n_tx, a.n_ch, c.nb, c.lmax, a.cx ? 2 : 1, c.guard, 0, mode,
-                                 mirror_copies(c.mir));
+                                 mirror_copies(c.mir), c.refs);
     hipError_t err;
     switch (mode) {
         case MODE_FORCES: err = launch_lds_et<MODE_FORCES>(a, c, et, ip, shm, s); break;

@@ -162,6 +162,16 @@ __device__ inline void lane_point(const DasArgs &a, const LdsCfg &c, int bx, int
     *iz = (((bz * c.bwz + wz) << a.lz) + lz) * c.zp + p - c.z_off;
 }
 
+// Samples from the delay at the middle depth of box bz to that at the middle depth
+// of its wavefront row r (depths inside the grid).
+__device__ inline int box_ref(const DasArgs &a, const LdsCfg &c, int bz, int r)
+{
+    const int tr = c.zp << a.lz, last = a.g.nz - 1, first = bz * c.bwz * tr - c.z_off;
+    const int lo = max(first, 0), hi = min(first + c.bwz * tr - 1, last);
+    const int rlo = min(max(first + r * tr, 0), last), rhi = min(first + (r + 1) * tr - 1, last);
+    return (int)rintf(c.ref_step * 0.5f * (float)(rlo + rhi - lo - hi));
+}
+
 // nref (folded HERCULES reads): fB then holds B - nref in one FP32 rounding; IQ
 // lanes keep the fraction of B there and floor(B) - nref in nB.
 template <int MODE, int NM, bool IQ>
@@ -702,11 +712,13 @@ __device__ inline void store_w0(const LdsCfg &c, const TraceDesc &td, int *w, in
 // byte address of slot `lane`'s window in buffer `quads` less (w0 - nR)
 // quads (modulo 2^32: the terms add floor(s) * 16 back, and the sum is the
 // address of quad floor(s) + nR - w0 of the window; QS quads per interval).
+// Each reference of the box (real data: refs of them) has its table, `w`, written
+// by the first wavefront of its row.
 template <int QS, int NM>
 __device__ inline void store_w0_addr(const LdsCfg &c, const TraceDesc &td, int *w, const float4 *quads,
-                                     int nR, int wave, int lane)
+                                     int nR, int refs, int wave, int lane)
 {
-    if (wave != 0 || lane >= NM * c.nb || lane % NM) return;
+    if (wave >= refs || lane >= NM * c.nb || lane % NM) return;
     w[lane / NM] = (int)(lds_addr(quads + (lane / NM) * c.lmax * QS) +
                          ((unsigned)(nR - td.w0) << (QS == 2 ? 5 : 4)));
 }
@@ -1023,7 +1035,8 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
     float *s_lo = s_rx + nch4;                     // [ntx4] tx_lo, then [nch4] rx_lo
     // (indexed from one base so that the compiler keeps them in LDS)
     int *s_w0 = reinterpret_cast<int *>(s_lo + (SEP ? ntx4 + nch4 : 0));
-    const int w0_stride = (c.nb + 3) & ~3;
+    const int w0_row = (c.nb + 3) & ~3;
+    const int w0_stride = HF && ET != ET_CF32 ? c.refs * w0_row : w0_row;
     float2 *s_hann = reinterpret_cast<float2 *>(s_w0 + 2 * w0_stride);
     float4 *bufbase = reinterpret_cast<float4 *>(s_hann + (MODE == MODE_HERCULES ? HANN_TAB_PAD : 0));
     constexpr int QS = ET == ET_CF32 ? 2 : 1;     // quads per sample interval
@@ -1066,11 +1079,16 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
         for (int t = tid; t < 2 * w0_stride; t += nthr) s_w0[t] = 0;
     // HF: nR = the sample of the two-way path txlo + zmax, near the middle of
     // the box's delays B (the same integer in every thread), so the lanes'
-    // folded positions B - nR + excess stay near the excess path's magnitude
+    // folded positions B - nR + excess stay near the excess path's magnitude;
+    // the wavefront rows of a deep box have references of their own beside it
     const int nR = HF ? (int)floorf(fmaf(box.txlo + fmaxf(box.zmax, 0.f), box.kf, -box.t0f)) : 0;
+    const int refs = HF && ET != ET_CF32 ? c.refs : 1;
+    const int row = refs > 1 ? wave % c.bwz : 0;
+    const int ref = refs > 1 ? nR + box_ref(a, c, bz, row) : nR;
     LaneL Lp[ZP];
 #pragma unroll
-    for (int p = 0; p < ZP; ++p) Lp[p] = lane_setup_l<MODE, NM, ET == ET_CF32>(a, c, bx, by, bz, wave, lane, p, HF ? &nR : nullptr);
+    for (int p = 0; p < ZP; ++p)
+        Lp[p] = lane_setup_l<MODE, NM, ET == ET_CF32>(a, c, bx, by, bz, wave, lane, p, HF ? &ref : nullptr);
     const LaneL &L = Lp[0];
     // largest rho^2 bound of the receive aperture over the lane's points
     float thr_l = Lp[0].thr;
@@ -1137,7 +1155,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
             stage_store<IP, QS, QM, GC, NM>(c, st, q0, wave, lane, nwaves);
         }
         if constexpr (HF)
-            store_w0_addr<QS, NM>(c, td, s_w0, q0, nR, wave, lane);
+            store_w0_addr<QS, NM>(c, td, s_w0 + row * w0_row, q0, ref, refs, wave, lane);
         else if constexpr (!FOLD)
             store_w0(c, td, s_w0, wave, lane);
     }
@@ -1190,7 +1208,7 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
             // from LDS -- no lane broadcasts (their SGPR results stall the wave)
             const unsigned hann = hann_base(s_hann);
             const cptr<float> txcol = as_const(a.tx_x) + cur.i0;
-            const int *wst = s_w0 + (bi & 1) * w0_stride;
+            const int *wst = s_w0 + (bi & 1) * w0_stride + row * w0_row;
             if constexpr (ZP == 2) {
                 // one trace per step already gives two independent terms
                 while (mask) {
@@ -1342,8 +1360,8 @@ __device__ inline void das_block(const DasArgs &a, const LdsCfg &c, int blk, int
         if (!nxt.valid) break;
         if constexpr (STAGE) stage_store<IP, QS, QM, GC, NM>(c, st, ((bi + 1) & 1) ? q1 : q0, wave, lane, nwaves);
         if constexpr (HF)
-            store_w0_addr<QS, NM>(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride, ((bi + 1) & 1) ? q1 : q0, nR, wave,
-                          lane);
+            store_w0_addr<QS, NM>(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride + row * w0_row,
+                                  ((bi + 1) & 1) ? q1 : q0, ref, refs, wave, lane);
         else if constexpr (!FOLD)
             store_w0(c, td_n, s_w0 + ((bi + 1) & 1) * w0_stride, wave, lane);
         __syncthreads();
@@ -1453,6 +1471,6 @@ static inline hipError_t allow_lds(const void *fn, size_t shm)
 }
 
 size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
-                 int nm = 1);
+                 int nm = 1, int refs = 1);
 
 }  // namespace bf

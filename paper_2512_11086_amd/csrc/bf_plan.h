@@ -89,7 +89,7 @@ hipError_t launch_das_lds(const DasArgs &a, const LdsCfg &c, int mode, int et, i
                           hipStream_t s);
 hipError_t launch_das_lds_fused(const DasArgs &a, const LdsCfg &c, int ip, hipStream_t s);
 size_t lds_bytes(int n_tx, int n_ch, int nb, int lmax, int qs, int guard, int adj, int mode,
-                 int nm = 1);
+                 int nm = 1, int refs = 1);
 hipError_t launch_das_lds_adjoint(const DasArgs &a, const LdsCfg &c, int mode, int ip,
                                   float *grad_c, hipStream_t s, int n_frames = 1);
 

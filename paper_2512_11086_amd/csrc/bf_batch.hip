@@ -125,15 +125,32 @@ static int build_batch(bf_plan plan)
     // that it still gives about four items per CU; each group writes a
     // partial image and a second kernel adds them in a fixed order.
     const long target_items = 4L * cus0;
-    std::vector<int> lds_ok(F, 0), groups(F, 1);
-    {
+    std::vector<int> lds_ok(F, 0), groups(F, 1), plain(F, 0);
+    std::vector<LdsCfg> cfgs(F);
+    // Whether a frame runs its own launch instead of its share of the persistent
+    // one: a frame of a class that would need the channel split, whose own
+    // launch (the single-frame kernel) gives two workgroups per CU already with
+    // the groups that fill the chip once (adj_groups; the forward launch may
+    // split further).  That launch, captured in the pass like the others,
+    // measured faster (a pair of 256 x 256 planes from 128 x 128 traces: 1.35 ms
+    // per pass persistent).
+    auto own_launch = [&](int f) {
+        const LdsCfg &c = cfgs[f];
+        return groups[f] > 1 && (long)c.blocks_x * c.blocks_y * c.blocks_z *
+                                        plan->frames[f]->adj_groups >= 2L * cus0;
+    };
+    auto classes = [&]() {
         std::vector<std::pair<long, long>> cls_boxes;   // (class key, boxes)
         std::vector<long> key(F, -1);
         for (int f = 0; f < F; ++f) {
             Frame &fr = *plan->frames[f];
             DasArgs a = fr.das_args(nullptr, nullptr, fr.p.c);
-            LdsCfg c;
-            if (fr.variant == BF_DAS_GATHER || !fr.lds_config(a, &c)) continue;
+            LdsCfg &c = cfgs[f];
+            lds_ok[f] = 0;
+            groups[f] = 1;
+            if (fr.variant == BF_DAS_GATHER ||
+                !(plain[f] ? fr.fit_config(a, MIRROR_NONE, &c, 0, nullptr, false) : fr.lds_config(a, &c)))
+                continue;
             lds_ok[f] = 1;
             key[f] = ((((long)fr.p.mode * 8 + fr.p.e_type) * 8 + fr.p.interp) * 4 + c.zp) * 8192 +
                      2048 * mirror_copies(c.mir) / 2 + 64 * c.bwx * c.bwy * c.bwz;
@@ -150,7 +167,37 @@ static int build_batch(bf_plan plan)
                     const long gmax = std::max(1, plan->frames[f]->p.n_ch / 4);
                     groups[f] = (int)std::min<long>(std::min<long>(G, 16), gmax);
                 }
+    };
+    classes();
+    // Mirror points split small persistent frames into classes that run one after
+    // the other.  Where the plain launches of all of them cost at most 5 % more,
+    // they run plain, as one class (31 x 31 x 77 points from 128 and 16 x 116
+    // traces with a plane, 2 % more: 865 us as one class, 1 042 as two; 46 x 46 x
+    // 97 from 16 to 128 x 117, 10 % more: 5 037 and 4 703).
+    for (int f = 0; f < F; ++f) {
+        if (!lds_ok[f] || plain[f] || cfgs[f].mir == MIRROR_NONE || groups[f] == 1 || own_launch(f)) continue;
+        const Frame &f0 = *plan->frames[f];
+        std::vector<int> set;
+        bool mixed = false;
+        double with = 0.0, without = 0.0;
+        for (int g = 0; g < F; ++g) {
+            const Frame &fg = *plan->frames[g];
+            if (!lds_ok[g] || fg.p.mode != f0.p.mode || fg.p.e_type != f0.p.e_type ||
+                fg.p.interp != f0.p.interp || groups[g] == 1 || own_launch(g))
+                continue;
+            LdsCfg c;
+            const DasArgs a = fg.das_args(nullptr, nullptr, fg.p.c);
+            if (!fg.fit_config(a, MIRROR_NONE, &c, 0, nullptr, false)) { mixed = false; break; }
+            mixed = mixed || mirror_copies(cfgs[g].mir) != mirror_copies(cfgs[f].mir);
+            const double traces = (double)fg.p.n_tx * fg.p.n_ch;
+            with += traces * fg.launch_cost(cfgs[g]);
+            without += traces * fg.launch_cost(c);
+            set.push_back(g);
+        }
+        if (mixed && without <= 1.05 * with)
+            for (int g : set) plain[g] = 1;
     }
+    classes();
     for (int f = 0; f < F; ++f) {
         Frame &fr = *plan->frames[f];
         if (!fr.d_e) {
@@ -168,20 +215,13 @@ static int build_batch(bf_plan plan)
         fi.channel_groups = 1;
         fi.decode_class = -1;
         fi.das_items = 0;
-        if (!lds_ok[f] || !fr.lds_config(a, &c)) {
+        if (lds_ok[f]) c = cfgs[f];
+        if (!lds_ok[f]) {
             b->gather_frames.push_back(f);
             const int st = fr.alloc_part();
             if (st != BF_OK) return st;
             memset(&c, 0, sizeof c);
-        } else if (groups[f] > 1 &&
-                   (long)c.blocks_x * c.blocks_y * c.blocks_z * fr.adj_groups >= 2L * cus0) {
-            // A frame of a class that would need the channel split, whose own
-            // launch (the single-frame kernel) gives two workgroups per CU
-            // already with the groups that fill the chip once (adj_groups; the
-            // forward launch may split further): that launch, captured in
-            // the pass like the others, measured faster than its share of the
-            // persistent launch (a pair of 256 x 256 planes from 128 x 128
-            // traces: 1.35 ms per pass persistent).
+        } else if (!plain[f] && own_launch(f)) {
             b->frame_lds.push_back(f);
             const int st = fr.alloc_part();
             if (st != BF_OK) return st;

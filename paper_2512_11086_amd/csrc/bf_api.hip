@@ -464,7 +464,10 @@ constexpr long PART_MAX_BYTES = 32l << 20;
 //    traces and two rows: below that the partial images cost more than the
 //    balance gains.  Another split, down to 96 traces, is taken where its rounds
 //    are 20 % cheaper: over 150 volumes 2.4 % slower than the best split timed,
-//    4.0 without this, 13.4 with the floor.
+//    4.0 without this, 13.4 with the floor.  FP32 volumes go back to
+//    the floor alone, and only without mirror points, where the aim can be the
+//    slower one (79 x 31 x 91 points from 12 x 76 traces: 3 groups 174 us, 4 198):
+//    their dL/dc shows another order of the sum as that of planes does.
 // The partial images stay within PART_MAX_BYTES.
 void Frame::choose_groups()
 {
@@ -525,7 +528,8 @@ void Frame::choose_groups()
     };
     double best = (hercules ? 0.8 : 0.88) * cost(G);
     const long low = hercules ? adj_groups : 1;
-    const long high = hercules ? std::min((long)p.n_tx * p.n_ch / 96, (long)p.n_ch / 2) : chunks;
+    long high = hercules ? std::min((long)p.n_tx * p.n_ch / 96, (long)p.n_ch / 2) : chunks;
+    if (hercules && p.e_type == BF_E_F32 && !p.iq) high = c.mir == MIRROR_NONE ? adj_groups : 0;
     for (long g = low; g <= std::min<long>(std::min<long>(high, 16), cap); ++g) {
         const long m = (long)chunks_of(g);
         if (!hercules && g != adj_groups && (chunks + m - 1) / m != g) continue;   // (whole chunks)

@@ -93,3 +93,14 @@ CASES = [
 def test_groups_follow_the_rounds_of_the_fullest_xcd(args, kw, low, high):
     o = _launch(*args, **kw)
     assert o.lds and low <= o.groups <= high
+
+
+def test_float_volumes_do_not_split_further_than_their_aim():
+    """Their images feed dL/dc; fewer groups only without mirror points."""
+    box = dict(half=3.2 * MM, z=(4 * MM, 35 * MM))
+    far = [_launch("hercules", 32, 0.2 * MM, 20e6, 16, 32, (65, 62, 85), e_type=t, **box).groups
+           for t in ("f32", "i32")]
+    assert far[0] == 2 < far[1]
+    # 79 x 31 x 91 points, receivers off the centre: 3 groups 174 us, 4 198
+    o = _launch("hercules", 128, 0.1 * MM, 30e6, 12, 76, (79, 31, 91), 5 * MM, (5 * MM, 30 * MM))
+    assert (o.mirrors, o.groups) == (0, 3)
